@@ -42,12 +42,14 @@ struct DedispVariant {
                      // 5: the same contraction with 8 channels x 4 residuals per step
                      // 6: layouts 5 and 4 mixed by trial range (per DM block)
                      // 7: quads of channels staged per residual pattern, v_sad_u8 sums
+                     // 8: matrix-core contraction over byte-aligned, channel-interleaved
+                     //    staging with 128-row strips (8 x 4 or 4 x 8 per DM block), see below
     int tile;        // output samples per work-group (time tile)
     int depth;       // staging buffers in the LDS ring (loads run depth - 1 steps ahead);
                      // layout 7: staging chunks per step (64 units of 16 bytes each)
     int max_tiles;   // layouts 4-6: a channel block spans at most 32 * max_tiles rows of t' (31 or 63)
 };
-constexpr int kNumDedispVariants = 25;
+constexpr int kNumDedispVariants = 26;
 static_assert(kNumDedispVariants <= AA_MAX_VARIANTS, "aa_batch_info_t::tune_ms holds every variant");
 
 // Matrix-core variants (layouts 4-6). Within a block of up to 32 trials (first trial d0)
@@ -119,6 +121,49 @@ constexpr int32_t kQuadNoRow = int32_t{1} << 30;
 constexpr int64_t kQuadMaxPitch = int64_t{1} << 28;   // four row pitches stay below kQuadNoRow
 constexpr int quad_lds_bytes(int chunks) { return 2 * chunks * 1024; }
 
+// Strip variant (layout 8): the contraction of the layouts 4-6 with the reference trial in
+// the middle of the block,
+//   s[d][c] = base[c] + E[d] + r[d][c],  base[c] = s[d0 + count / 2][c],
+// so that residuals drift over at most half a block and a channel block holds about twice
+// the channels. A group is 8 consecutive channels in two quads of 4; a substep is one matrix
+// op's channels (8 for R = 4 residuals, 4 for R = 8), and channel blocks ("runs") end
+// between substeps. Row c is staged from its exact start rs[c] = base[c] + min E (may be
+// negative down to 1 - R, or exceed the input's end, where only unstored outputs read).
+// A strip is 128 consecutive rows of t'; a run needs ceil((tile + max e) / 128) of them.
+// Tables:
+//   base: rs[nblk][nchan_pad], 0 for channels past nchan
+//   records (d_offs): per block nchan_pad / 8 group records of 64 dwords, one per lane
+//     (m = lane & 31 the trial, h = lane >> 5 the half), then as many info dwords, padded to
+//     a multiple of 64:
+//     R = 4: byte i holds 8 r of channel 4 h + i in its low 5 bits; the top 3 bits of the
+//            four bytes hold e (3 bits each, byte 0 lowest)
+//     R = 8: bits 3 i .. 3 i + 2 hold r of channel 4 (i / 2) + 2 h + i % 2 (substep i / 2);
+//            bits 12-21 and 22-31 hold e of the runs of substeps 0 and 1
+//   info: bit 0 / 1: substep 0 / 1 is its run's last (bit 1 copies bit 0 for R = 4);
+//     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e;
+//     bit 30: a row of the group needs more than kStripNarrowBytes staged bytes
+constexpr int kStripTile = 832;
+constexpr int kStripRows = 128;
+constexpr int kStripWaves = 12;          // contracting waves, one strip each
+constexpr int kStripStages = 2;          // load stages of the staging waves
+constexpr int kStripNarrowBytes = 1016;  // staged bytes of a row in two passes of 127 dwords
+constexpr int kStripWideBytes = 1524;    // and in three
+constexpr int kStripRowDwords = 388;     // LDS entries per row: 12 strips, 3 to read past, a spare one
+constexpr uint32_t kStripNoRow = 0x7fff0000u;           // row offset (and end) of a unit's load range
+constexpr int64_t kStripMaxPitch = int64_t{1} << 26;    // 16 pitches and a row start stay below it
+// channels covered by the tables: whole rounds of kStripStages steps of two groups, and the
+// group that the last step reads ahead
+constexpr int strip_nchan_pad(int nchan) {
+    return 16 * kStripStages * (((nchan + 7) / 8 + 2 * kStripStages) / (2 * kStripStages)) + 16 * kStripStages;
+}
+constexpr int strip_lds_bytes(int tile) { return (tile + 2) * 32 * 4 + 4 * (8 * kStripRowDwords * 4 + 256); }
+// largest e whose rows fit the strips, their window reads the staged bytes, and e its field
+constexpr int strip_spread(int tile) {
+    return kStripRows * kStripWaves - tile < kStripWideBytes - 7 - tile ? kStripRows * kStripWaves - tile
+                                                                        : kStripWideBytes - 7 - tile;
+}
+static_assert(strip_spread(kStripTile) <= 1023 && strip_lds_bytes(kStripTile) <= 163840, "strip variant limits");
+
 extern const DedispVariant kDedispVariants[kNumDedispVariants];
 // Input row pitches a variant can take (the quad variants address four rows from one
 // 32-bit range).
@@ -135,10 +180,10 @@ struct DmBlock {
     int32_t first;   // first DM trial of the block
     int32_t count;   // trials in the block (<= waves * dpw)
     int32_t row;     // LDS row length (bytes) the block needs, multiple of 16 (layouts 0-3)
-    int32_t rs_lo;   // layouts 4-6: smallest and largest staged-row start over the block's
+    int32_t rs_lo;   // layouts 4-6, 8: smallest and largest staged-row start over the block's
     int32_t rs_hi;   // channels, relative to the time tile (0 for the other layouts)
-    int32_t cps;     // layouts 4-6: channels per matrix step of this block (4 or 8)
-    int32_t rec256;  // layouts 4-7: offset of the block's records in 256-byte units
+    int32_t cps;     // layouts 4-6, 8: channels per matrix step of this block (4 or 8)
+    int32_t rec256;  // layouts 4-8: offset of the block's records in 256-byte units
 };
 
 // Per-variant tables. For block b and channel c:
@@ -213,6 +258,11 @@ int prepare_mixed_split(aa_plan_s* p, int variant, int split);
 // units) and the records [block][nq + 1][quad_rec_dwords(chunks)].
 int build_quad_tables(const aa_plan_s* p, int tile, int chunks, std::vector<DmBlock>& blocks,
                       std::vector<int32_t>& rec);
+// Host tables of the strip variant: DM blocks (cps 8 or 4: channels per matrix op; rec256 in
+// 256-byte units), row starts [nblk][nchan rounded up to 8] and the records. shape 0 takes
+// the cheaper shape per block by the cost estimate, 8 or 4 forces one.
+int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBlock>& blocks, std::vector<int32_t>& rs,
+                       std::vector<uint32_t>& rec);
 void free_tables(DedispTables& t);
 // Launchers (dedisp.hip, sps.hip). Arguments are validated by the callers.
 int launch_dedisperse(const aa_plan_s* p, int variant, const uint8_t* d_in, int64_t in_pitch, int64_t n_in,

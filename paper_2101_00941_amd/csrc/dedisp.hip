@@ -22,30 +22,10 @@
 //    variants below recast each block of 32 trials as an exact one-hot int8 contraction
 //    on the matrix cores (v_mfma_i32_32x32x32_i8), which is faster on this chip although
 //    most of its multiply-accumulates are by zero; see dedisp_mfma_tile.
-#include "aa_internal.h"
-#include "xcd.h"
+#include "dedisp_device.h"
 
 namespace aa {
 namespace {
-
-// A DM block's table entry, read through the constant address space: it is the same in
-// every lane and read-only for the launch, so its loads are scalar even where the table
-// pointer comes from memory (the persistent batch kernel reads it from the beam's
-// argument block).
-__device__ __forceinline__ DmBlock load_block(const DmBlock* blocks, int blk) {
-    static_assert(sizeof(DmBlock) % 4 == 0, "a DM block entry is whole dwords");
-    typedef const __attribute__((address_space(4))) int32_t* word_ptr;
-    const word_ptr p = (word_ptr)(const void*)(blocks + blk);
-    int32_t w[sizeof(DmBlock) / 4];
-#pragma unroll
-    for (int i = 0; i < static_cast<int>(sizeof(DmBlock) / 4); ++i) w[i] = p[i];
-    DmBlock b;
-    __builtin_memcpy(&b, w, sizeof(b));
-    return b;
-}
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) void lds_void;
 
 // Work-group i runs on XCD i % 8. Give each XCD a contiguous run of logical tiles
 // (adjacent DM blocks of the same time tile), so that their overlapping input rows
@@ -328,9 +308,6 @@ __device__ __forceinline__ void dedisp_tile(const DedispArgs& A, int blk, int64_
         }
     }
 }
-
-typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
 
 // s_waitcnt vmcnt(n) for a wave-uniform n in [0, 24].
 template <int N>
@@ -829,8 +806,6 @@ __device__ __forceinline__ void lds_step_barrier() {
     asm volatile("" ::: "memory");
 }
 
-constexpr int kRawBufferFlags = 0x00020000;   // word 3 of a gfx9 buffer resource: raw 32-bit data
-
 template <int W, int J, int CPW>
 __device__ __forceinline__ void dedisp_quad_tile(const DedispArgs& A, int blk, int64_t t0) {
     constexpr int NT = 64 * W, CH = W * CPW, BUFB = CH * 1024, RD = quad_rec_dwords(CH);
@@ -1005,53 +980,24 @@ __global__ __launch_bounds__(64 * W, WPE) void dedisp_kernel(DedispArgs a) {
 }
 
 // Batched persistent launch: a grid of resident work-groups pulls (beam, DM block,
-// time tile) items from one device counter until the items run out, so beams of any
-// shape share one launch. Consecutive items are adjacent DM blocks of the same tile
-// of the same beam (their input rows overlap). A work-group reads the item index from
-// the counter, finds its beam by binary search over item_begin, and exits when the
-// index passes the total: every work-group reaches that exit.
+// time tile) items, so beams of any shape share one launch.
 template <int DPW, int W, int LAYOUT, int TILE = kTimeTile, int DEPTH = 2, int MAXT = 63, int WPE = 1>
 __global__ __launch_bounds__(64 * W, WPE) void dedisp_batch_kernel(const DedispArgs* __restrict__ args,
                                                               const int64_t* __restrict__ item_begin, int nbeams,
                                                               int64_t total, unsigned long long* counter) {
-    __shared__ int64_t item;
-    for (;;) {
-        if (threadIdx.x == 0) item = static_cast<int64_t>(atomicAdd(counter, 1ull));
-        __syncthreads();
-        // the item index is the same in every lane: keep it in scalar registers
-        const uint64_t itu = static_cast<uint64_t>(item);
-        const int64_t it = static_cast<int64_t>(
-            (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(itu >> 32))) << 32) |
-            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(itu))));
-        __syncthreads();
-        if (it >= total) break;
-        int lo = 0, hi = nbeams - 1;
-        while (lo < hi) {
-            const int mid = (lo + hi + 1) >> 1;
-            if (item_begin[mid] <= it) lo = mid; else hi = mid - 1;
-        }
-        // the beam is the same in every lane; stating it keeps the beam's arguments and
-        // the tile's step records in scalar registers
-        lo = __builtin_amdgcn_readfirstlane(lo);
-        const DedispArgs a = args[lo];
-        const int64_t local = it - item_begin[lo];
+    batch_items(args, item_begin, nbeams, total, counter, [](const DedispArgs& a, int blk, int64_t tile) {
         if constexpr (LAYOUT == 7)
-            dedisp_quad_tile<W, DPW, DEPTH>(a, static_cast<int>(local % a.nblk), (local / a.nblk) * TILE);
+            dedisp_quad_tile<W, DPW, DEPTH>(a, blk, tile * TILE);
         else if constexpr (LAYOUT == 6)
-            dedisp_mfma_mixed<W, TILE, DEPTH, MAXT>(a, static_cast<int>(local % a.nblk), (local / a.nblk) * TILE);
+            dedisp_mfma_mixed<W, TILE, DEPTH, MAXT>(a, blk, tile * TILE);
         else if constexpr (LAYOUT == 4 || LAYOUT == 5)
-            dedisp_mfma_tile<W, TILE, DEPTH, MAXT, mfma_cps(LAYOUT)>(a, static_cast<int>(local % a.nblk),
-                                                                     (local / a.nblk) * TILE);
+            dedisp_mfma_tile<W, TILE, DEPTH, MAXT, mfma_cps(LAYOUT)>(a, blk, tile * TILE);
         else
-            dedisp_tile<DPW, W, LAYOUT>(a, static_cast<int>(local % a.nblk), (local / a.nblk) * kTimeTile);
-        __syncthreads();   // the next item restages LDS buffer 0
-    }
+            dedisp_tile<DPW, W, LAYOUT>(a, blk, tile * kTimeTile);
+    });
 }
 
 __global__ void reset_counter_kernel(unsigned long long* c) { *c = 0ull; }
-
-typedef void (*DedispFn)(DedispArgs);
-typedef void (*DedispBatchFn)(const DedispArgs*, const int64_t*, int, int64_t, unsigned long long*);
 
 // Indexed by DedispVariant::id (tiling.cpp); layout 4-6 entries repeat the variant's
 // time tile, depth and channel-block span; layout 7 entries are <samples per lane, waves,
@@ -1062,8 +1008,12 @@ typedef void (*DedispBatchFn)(const DedispArgs*, const int64_t*, int, int64_t, u
         K<4, 8, 4, 512, 3, 31, 4>, K<2, 16, 4, 512, 3, 31, 8>, K<4, 8, 4, 480, 4, 31, 4>, K<2, 16, 5, 864, 3, 63>, \
         K<2, 16, 4, 960, 4, 63>, K<2, 16, 4, 896, 5, 63>, K<2, 16, 6, 864, 3, 63>, K<2, 4, 7, 512, 4, 0, 4>, \
         K<2, 8, 7, 1024, 4, 0, 4>, K<1, 16, 7, 1024, 2, 0, 8>, K<1, 8, 7, 512, 2, 0, 8>
-const DedispFn kKernels[kNumDedispVariants] = {AA_VARIANTS(dedisp_kernel)};
-const DedispBatchFn kBatchKernels[kNumDedispVariants] = {AA_VARIANTS(dedisp_batch_kernel)};
+const DedispFn kKernels[] = {AA_VARIANTS(dedisp_kernel)};
+const DedispBatchFn kBatchKernels[] = {AA_VARIANTS(dedisp_batch_kernel)};
+DedispFn kernel_of(int variant) { return kDedispVariants[variant].layout == 8 ? kStripKernel : kKernels[variant]; }
+DedispBatchFn batch_kernel_of(int variant) {
+    return kDedispVariants[variant].layout == 8 ? kStripBatchKernel : kBatchKernels[variant];
+}
 #undef AA_VARIANTS
 
 }  // namespace
@@ -1106,7 +1056,7 @@ int launch_dedisperse(const aa_plan_s* p, int variant, const uint8_t* d_in, int6
     const int64_t grid = a.ntile * a.nblk;
     if (grid > 0x7fffffff) return fail(AA_EINVAL, "aa_dedisperse: too many tiles for one launch");
     const size_t lds = V.layout >= 4 ? static_cast<size_t>(V.lds_bytes) : static_cast<size_t>(2 * kChanPerPass) * T.max_row;
-    hipLaunchKernelGGL(kKernels[variant], dim3(static_cast<unsigned>(grid)), dim3(64 * V.waves), lds, stream, a);
+    hipLaunchKernelGGL(kernel_of(variant), dim3(static_cast<unsigned>(grid)), dim3(64 * V.waves), lds, stream, a);
     AA_HIP(hipGetLastError());
     return AA_OK;
 }
@@ -1118,12 +1068,12 @@ int launch_dedisperse_batch(int variant, const DedispArgs* d_args, const int64_t
     int dev = 0, cus = 0, per_cu = 0;
     AA_HIP(hipGetDevice(&dev));
     AA_HIP(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-    AA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kBatchKernels[variant], 64 * V.waves, lds));
+    AA_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, batch_kernel_of(variant), 64 * V.waves, lds));
     if (per_cu < 1) return fail(AA_EINVAL, "batched dedispersion: the kernel does not fit on a CU");
     const int64_t grid = std::min<int64_t>(static_cast<int64_t>(cus) * per_cu, std::max<int64_t>(total, 1));
     hipLaunchKernelGGL(reset_counter_kernel, dim3(1), dim3(1), 0, stream, d_counter);
     AA_HIP(hipGetLastError());
-    hipLaunchKernelGGL(kBatchKernels[variant], dim3(static_cast<unsigned>(grid)), dim3(64 * V.waves), lds, stream,
+    hipLaunchKernelGGL(batch_kernel_of(variant), dim3(static_cast<unsigned>(grid)), dim3(64 * V.waves), lds, stream,
                        d_args, d_item_begin, nbeams, total, d_counter);
     AA_HIP(hipGetLastError());
     return AA_OK;

@@ -1,0 +1,75 @@
+// Device-side pieces shared by the dedispersion kernels.
+#pragma once
+
+#include "aa_internal.h"
+#include "xcd.h"
+
+namespace aa {
+
+typedef void (*DedispFn)(DedispArgs);
+typedef void (*DedispBatchFn)(const DedispArgs*, const int64_t*, int, int64_t, unsigned long long*);
+// The strip kernels (strip.hip).
+extern const DedispFn kStripKernel;
+extern const DedispBatchFn kStripBatchKernel;
+
+namespace {
+
+// A DM block's table entry, read through the constant address space: it is the same in
+// every lane and read-only for the launch, so its loads are scalar even where the table
+// pointer comes from memory (the persistent batch kernel reads it from the beam's
+// argument block).
+__device__ __forceinline__ DmBlock load_block(const DmBlock* blocks, int blk) {
+    static_assert(sizeof(DmBlock) % 4 == 0, "a DM block entry is whole dwords");
+    typedef const __attribute__((address_space(4))) int32_t* word_ptr;
+    const word_ptr p = (word_ptr)(const void*)(blocks + blk);
+    int32_t w[sizeof(DmBlock) / 4];
+#pragma unroll
+    for (int i = 0; i < static_cast<int>(sizeof(DmBlock) / 4); ++i) w[i] = p[i];
+    DmBlock b;
+    __builtin_memcpy(&b, w, sizeof(b));
+    return b;
+}
+
+constexpr int kRawBufferFlags = 0x00020000;   // word 3 of a gfx9 buffer resource: raw 32-bit data
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) void lds_void;
+
+typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
+typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
+
+// The batched persistent launch: a work-group pulls item indexes from the device counter
+// until they run out (every work-group reaches that exit) and runs tile(args, block, t0) of
+// the item's beam, found by binary search over item_begin. Consecutive items are adjacent
+// DM blocks of the same time tile of the same beam (their input rows overlap).
+template <class Tile>
+__device__ __forceinline__ void batch_items(const DedispArgs* __restrict__ args, const int64_t* __restrict__ item_begin,
+                                            int nbeams, int64_t total, unsigned long long* counter, Tile tile) {
+    __shared__ int64_t item;
+    for (;;) {
+        if (threadIdx.x == 0) item = static_cast<int64_t>(atomicAdd(counter, 1ull));
+        __syncthreads();
+        // the item index is the same in every lane: keep it in scalar registers
+        const uint64_t itu = static_cast<uint64_t>(item);
+        const int64_t it = static_cast<int64_t>(
+            (static_cast<uint64_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(itu >> 32))) << 32) |
+            static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<uint32_t>(itu))));
+        __syncthreads();
+        if (it >= total) break;
+        int lo = 0, hi = nbeams - 1;
+        while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (item_begin[mid] <= it) lo = mid; else hi = mid - 1;
+        }
+        // the beam is the same in every lane; stating it keeps the beam's arguments and
+        // the tile's step records in scalar registers
+        lo = __builtin_amdgcn_readfirstlane(lo);
+        const DedispArgs a = args[lo];
+        const int64_t local = it - item_begin[lo];
+        tile(a, static_cast<int>(local % a.nblk), local / a.nblk);
+        __syncthreads();   // the next item restages the LDS
+    }
+}
+
+}  // namespace
+}  // namespace aa

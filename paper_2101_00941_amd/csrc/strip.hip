@@ -1,0 +1,409 @@
+// Strip kernels (layout 8): brute-force dedispersion as an exact one-hot int8 contraction on
+// the matrix cores, arranged so that the matrix cores and not the step around them set the
+// pace. The contraction itself (residual windows of the input against a one-hot matrix per
+// channel group, partial sums on a shifted time axis t', added into the output tile at t' - e
+// when a run of channels ends) is that of the layouts 4-6; tables in aa_internal.h.
+//  * Sixteen waves per work-group, four per SIMD: 12 contract and 4 stage the input rows. A
+//    wave that does both is slowed by its own instruction stream (address arithmetic, loads
+//    that queue for the address unit): measured, such a step took 1400 cycles for 512 of
+//    matrix work.
+//  * A contracting wave owns one strip of 128 rows of t': row 4 R + j of the strip is row R
+//    of its matrix tile j. A lane then needs, for its four tiles, one dword-aligned span of
+//    each channel (2 dwords for R = 4 residuals, 3 for R = 8), and tile j's window is that
+//    span shifted by the constant j bytes (v_alignbyte_b32).
+//  * Rows are staged through registers and aligned to their exact start, four channels to a
+//    16-byte LDS entry per dword of time, with the sign flip (XOR 0x80) done once per staged
+//    dword. So the operand reads are wide LDS reads at constant offsets: no window
+//    addresses, phases or sign flips remain in the matrix loop.
+//  * A step is two groups of 8 channels and one barrier. The ring holds four groups: in step
+//    k the contracting waves use groups 2 k and 2 k + 1 and read the operands of 2 k + 1 and
+//    2 k + 2, while the staging waves fill the places of 2 k + 3 and 2 k + 4.
+#include "dedisp_device.h"
+
+namespace aa {
+namespace {
+
+constexpr int kContract = kStripWaves;              // contracting waves
+constexpr int kStage = 4;                           // staging waves
+constexpr int kThreads = 64 * (kContract + kStage);
+constexpr int kAcc0 = 128;                          // LDS: accumulator rows -1 .. TILE, row 0 here
+constexpr int kQuadBytes = kStripRowDwords * 16;    // four staged rows
+constexpr int kGroupBytes = 2 * kQuadBytes;
+constexpr int strip_ring(int tile) { return (tile + 2) * 128; }
+constexpr int strip_recs(int tile) { return strip_ring(tile) + 4 * kGroupBytes; }   // 256 bytes per group
+
+// Entry td of a quad lies at td with its low bit flipped in every other group of 8, so that
+// lanes that store two entries 32 bytes apart hit all banks.
+__device__ __forceinline__ int entry_at(int td) { return 16 * (td ^ ((td >> 3) & 1)); }
+
+__device__ __forceinline__ void step_barrier() {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Adds a wave's strip q of a finished run into the accumulator tile and clears its
+// accumulators: register i of tile j of lane (m, h) is row 128 q + 4 (8 (i / 4) + 4 h + i % 4)
+// + j of t', trial m, and goes to t = t' - e; rows outside [0, TILE) are clamped to the
+// discarded rows -1 and TILE. A wave's 64 adds hit 32 banks twice each, for any e. The LDS
+// takes one add instruction per 4.2 cycles (measured, and the same for stores), which hides
+// the clamps of the four SIMDs.
+template <int TILE>
+__device__ __forceinline__ void strip_flush(i32x16 (&acc)[4], int q, int m, int h, int e, uint32_t row0) {
+    const int lo = static_cast<int>(row0) + 4 * m - 128, hi = static_cast<int>(row0) + 4 * m + 128 * TILE;
+    const int base = lo + 128 + 128 * (kStripRows * q + 16 * h - e);
+#pragma unroll
+    for (int i = 0; i < 16; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int at = min(max(base + 128 * (4 * (8 * (i >> 2) + (i & 3)) + j), lo), hi);
+            asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(acc[j][i]) : "memory");
+        }
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = i32x16{};
+}
+
+// The staging waves. Unit n is the pair of groups 2 n - 1 and 2 n (16 channels, four quads);
+// wave p stages quad p of every unit, PASSES loads of two dwords per lane and row. A lane
+// needs its successor's first dword to align its own two, so a pass yields 127 dwords.
+// EDGE: rows of the tile may start before sample 0 or run past the input's end (or row
+// offsets do not fit 31 bits).
+template <int TILE, bool EDGE>
+__device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& b, int blk, int64_t t0, uint8_t* lds,
+                                            int p, int lane, int K) {
+    constexpr int D = kStripStages, PASSES = 3, VALID = 127;
+    const int64_t pitch = A.in_pitch;
+    const uint32_t* const recs = reinterpret_cast<const uint32_t*>(A.offs) + static_cast<int64_t>(b.rec256) * 64;
+    const uint32_t* const infos = recs + static_cast<int64_t>(A.nchan_pad >> 3) * 64;
+    const int32_t* const rsv = A.base + static_cast<int64_t>(blk) * A.nchan_pad;
+    // unit n's first channel is 16 n - 8; this wave's quad
+    const int c0 = 4 * p - 8;
+    const int group = p >> 1;                         // of the unit
+    int wdst[PASSES][2];
+#pragma unroll
+    for (int s = 0; s < PASSES; ++s)
+#pragma unroll
+        for (int l = 0; l < 2; ++l)   // (a pass's last dword lacks its successor: into a spare entry)
+            wdst[s][l] = strip_ring(TILE) + (p & 1) * kQuadBytes +
+                         entry_at(2 * lane + l < VALID ? VALID * s + 2 * lane + l : kStripRowDwords - 1);
+
+    // One buffer resource per unit, based 16 bytes before its first row at the time tile; a
+    // row is reached through the scalar offset, which the range check counts: channels that
+    // do not exist carry an offset beyond the range and read zeros (they enter the sums as
+    // -128 per channel like every zero byte, and the final correction counts them). An EDGE
+    // tile takes a resource per row and keeps every load inside [0, n_in16) of it: a lane that
+    // would read outside moves to the nearest dword inside, and its bytes are shifted back to
+    // their places when they are written to LDS (bytes from outside only reach outputs that
+    // are not stored).
+    const uint8_t* sbase = EDGE ? A.in + c0 * pitch : A.in + t0 - 16 - 8 * pitch;
+    int nunit = 0;             // next unit to load
+    // per-unit tables, 64 units at a time, lane l holding unit 64 n + l
+    u32x4 off_tab{};           // offsets of the quad's rows from the unit's base
+    uint32_t info_tab = 0;     // infos of the wave's group
+    uint32_t st[D][PASSES][2][4];   // dwords in flight, [stage][pass][dword][channel]
+    uint32_t st_rec[D];        // record dwords in flight (waves 0 and 1: of group `p` of the unit)
+    uint32_t st_phase[D][4];   // bytes of each row before its start in its first dword
+    int st_lo[D][4], st_hi[D][4];   // EDGE: bounds of each row's byte positions
+    const __amdgpu_buffer_rsrc_t rec_rs = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<uint32_t*>(recs), 0, 256 * (A.nchan_pad >> 3), kRawBufferFlags);
+    auto issue = [&](int s) {
+        if ((nunit & 63) == 0) {
+            const int c = 16 * (nunit + lane) + c0;
+            const bool in = c >= 0 && c < A.nchan_pad;
+            off_tab = in ? *reinterpret_cast<const u32x4*>(rsv + c) : u32x4{0u, 0u, 0u, 0u};
+            info_tab = in ? infos[2 * (nunit + lane) - 1 + group] : 0u;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if constexpr (!EDGE) off_tab[i] += 16u + static_cast<uint32_t>((4 * p + i) * pitch);
+                if (c < 0 || c + i >= A.nchan) off_tab[i] = kStripNoRow;
+            }
+            // wait for the tables here, so that the units that do not load them need no wait
+            asm volatile("" : "+v"(off_tab), "+v"(info_tab));
+        }
+        const int sl = nunit & 63;
+        const bool wide = ((__builtin_amdgcn_readlane(static_cast<int>(info_tab), sl) >> 30) & 1) != 0;
+        uint32_t so[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) so[i] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(off_tab[i]), sl));
+        const int voff = 8 * lane;
+        if constexpr (!EDGE) {
+            // (the last pass of a narrow group loads an empty range)
+            const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint8_t*>(sbase), 0, static_cast<int>(kStripNoRow), kRawBufferFlags);
+            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint8_t*>(sbase), 0, wide ? static_cast<int>(kStripNoRow) : 0, kRawBufferFlags);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) st_phase[s][i] = so[i] & 3u;
+#pragma unroll
+            for (int q = 0; q < PASSES; ++q)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const auto x = __builtin_amdgcn_raw_buffer_load_b64(q == PASSES - 1 ? rw : rs, voff + 4 * VALID * q,
+                                                                        so[i] & ~3u, 0);
+                    st[s][q][0][i] = x[0];
+                    st[s][q][1][i] = x[1];
+                }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const bool real = so[i] != kStripNoRow;
+                const int64_t first = t0 + static_cast<int32_t>(so[i]);
+                const int hi = real ? static_cast<int>(min(A.n_in16 - 4 - first, int64_t{1} << 20)) : 1 << 20;
+                const int lo = real ? (first < 0 ? static_cast<int>(-first) : min(hi, 0)) : 0;
+                st_lo[s][i] = lo;
+                st_hi[s][i] = hi;
+                const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+                    const_cast<uint8_t*>(sbase + i * pitch + (real ? first + lo : 0)), 0, real ? hi - lo + 4 : 0,
+                    kRawBufferFlags);
+#pragma unroll
+                for (int q = 0; q < PASSES; ++q)
+#pragma unroll
+                    for (int l = 0; l < 2; ++l)
+                        st[s][q][l][i] = __builtin_amdgcn_raw_buffer_load_b32(
+                            rs, min(max(voff + 4 * (VALID * q + l), lo), hi) - lo, 0, 0);
+            }
+        }
+        st_rec[s] = __builtin_amdgcn_raw_buffer_load_b32(rec_rs, 4 * lane, 256 * (2 * nunit - 1 + (p & 1)), 0);
+        ++nunit;
+        sbase += 16 * pitch;
+    };
+    // unit n from stage s into its places of the ring (group 2 n - 1 at place (2 n) % 4)
+    auto write = [&](int s, int n) {
+        uint8_t* const dst = lds + (((2 * n) & 3) + group) * kGroupBytes;
+#pragma unroll
+        for (int q = 0; q < PASSES; ++q)
+#pragma unroll
+            for (int l = 0; l < 2; ++l) {
+                u32x4 o;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    uint32_t v = st[s][q][l][i];
+                    if constexpr (!EDGE) {
+                        // the row's bytes start `phase` bytes into the loaded dwords
+                        const uint32_t next = l == 0 ? st[s][q][1][i]
+                                                     : static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
+                                                           0, static_cast<int>(st[s][q][0][i]), 0x130, 0xf, 0xf, true));
+                        v = __builtin_amdgcn_alignbyte(next, v, st_phase[s][i]);
+                    } else {
+                        const int want = 8 * lane + 4 * (VALID * q + l);
+                        const int d = want - min(max(want, st_lo[s][i]), st_hi[s][i]);
+                        v = d > 0 ? (d < 4 ? v >> (8 * d) : 0u) : d < 0 ? (d > -4 ? v << (-8 * d) : 0u) : v;
+                    }
+                    o[i] = v ^ 0x80808080u;
+                }
+                *reinterpret_cast<u32x4*>(dst + wdst[q][l]) = o;
+            }
+        if (p < 2)
+            *reinterpret_cast<uint32_t*>(lds + strip_recs(TILE) + 256 * (((2 * n) & 3) + p) + 4 * lane) = st_rec[s];
+    };
+
+#pragma unroll
+    for (int s = 0; s < D; ++s) issue(s);
+    write(0, 0);
+    issue(0);
+    write(1, 1);
+    issue(1);
+    step_barrier();
+    // (the loop's own waits are counted only if nothing is in flight where it is entered)
+    __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
+    // whole rounds of D units, so that the loop has one exit: the waits for a stage's loads
+    // are counted over the loads issued after it on every path, and an exit per unit would
+    // join states in which fewer are
+    int k = 0;
+    do {
+#pragma unroll
+        for (int s = 0; s < D; ++s) {
+            step_barrier();
+            write((s + 2) % D, k + 2);
+            issue((s + 2) % D);
+            ++k;
+        }
+    } while (k < K);
+}
+
+// The contracting waves: strip `wave` of every run that has it.
+template <int TILE, int CPS>
+__device__ __forceinline__ void strip_contract(const DedispArgs& A, const DmBlock& b, uint8_t* lds, int wave, int lane,
+                                               int K) {
+    constexpr int NSUB = 8 / CPS;                     // matrix substeps per group
+    constexpr int NE = CPS == 8 ? 2 : 3;              // entries per window
+    typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+    const int m = lane & 31, h = lane >> 5;
+    const uint32_t row0 = static_cast<uint32_t>(
+        reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)(lds + kAcc0)));
+    const uint32_t* const infos = reinterpret_cast<const uint32_t*>(A.offs) + static_cast<int64_t>(b.rec256) * 64 +
+                                  static_cast<int64_t>(A.nchan_pad >> 3) * 64;
+    const int ngroups = 2 * K;
+
+    // operand dwords of the next group and its record
+    uint32_t a[CPS == 8 ? 8 : 12], rec_next = 0;
+    const uint8_t* rsrc[NE];
+#pragma unroll
+    for (int i = 0; i < NE; ++i)
+        rsrc[i] = lds + strip_ring(TILE) + (CPS == 8 ? h * kQuadBytes : 8 * h) + entry_at(32 * wave + m + i);
+    auto read = [&](int g) {
+        const int off = ((g + 1) & 3) * kGroupBytes;
+        rec_next = *reinterpret_cast<const uint32_t*>(lds + strip_recs(TILE) + 256 * ((g + 1) & 3) + 4 * lane);
+        if constexpr (CPS == 8) {
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const u32x4 x = *reinterpret_cast<const u32x4*>(rsrc[i] + off);
+#pragma unroll
+                for (int c = 0; c < 4; ++c) a[4 * i + c] = x[c];
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int i = 0; i < 3; ++i) {
+                    const u32x2 x = *reinterpret_cast<const u32x2*>(rsrc[i] + off + u * kQuadBytes);
+                    a[6 * u + 2 * i] = x[0];
+                    a[6 * u + 2 * i + 1] = x[1];
+                }
+        }
+    };
+    uint32_t info_tab = infos[min(lane, ngroups - 1)];   // lane l: group 64 n + l
+    auto info_of = [&](int g) {
+        if ((g & 63) == 0) {
+            info_tab = infos[min(g + lane, ngroups - 1)];
+            asm volatile("" : "+v"(info_tab));
+        }
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(info_tab), g & 63));
+    };
+    auto strips = [](uint32_t info, int u) { return static_cast<int>((info >> (2 + 4 * u)) & 15u) + 1; };
+    auto strips_any = [&](uint32_t info) { return NSUB == 1 ? strips(info, 0) : max(strips(info, 0), strips(info, 1)); };
+
+    i32x16 acc[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[j] = i32x16{};
+    step_barrier();
+    uint32_t info1 = info_of(0);
+    read(0);
+
+    // group g: windows from the operands read one group ahead, the next group's reads, matrix ops
+    auto contract = [&](int g) {
+        const uint32_t info = info1, rec = rec_next;
+        info1 = info_of(g + 1);
+#pragma unroll
+        for (int u = 0; u < NSUB; ++u) {
+            const bool on = wave < strips(info, u);
+            i32x4 w[4], B;
+            if (on) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    if constexpr (CPS == 8) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i)
+                            w[j][i] = static_cast<int32_t>(j == 0 ? a[i] : __builtin_amdgcn_alignbyte(a[4 + i], a[i], j));
+                    } else {
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const uint32_t x0 = a[6 * u + i], x1 = a[6 * u + 2 + i], x2 = a[6 * u + 4 + i];
+                            w[j][2 * i] = static_cast<int32_t>(j == 0 ? x0 : __builtin_amdgcn_alignbyte(x1, x0, j));
+                            w[j][2 * i + 1] = static_cast<int32_t>(j == 0 ? x1 : __builtin_amdgcn_alignbyte(x2, x1, j));
+                        }
+                    }
+                }
+                if constexpr (CPS == 8) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) B[i] = static_cast<int32_t>(1u << ((rec >> (8 * i)) & 31u));
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 2; ++j) {
+                        const uint32_t r = (rec >> (3 * (2 * u + j))) & 7u;
+                        const uint32_t one = 1u << (8u * (r & 3u));
+                        B[2 * j] = static_cast<int32_t>(r < 4u ? one : 0u);
+                        B[2 * j + 1] = static_cast<int32_t>(r < 4u ? 0u : one);
+                    }
+                }
+            }
+            if (u == NSUB - 1 && wave < strips_any(info1)) read(g + 1);
+            if (on) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[j], B, acc[j], 0, 0, 0);
+                if ((info >> u) & 1u) {
+                    // the run ends here: add its strip into the accumulator tile
+                    int e;
+                    if constexpr (CPS == 8)
+                        e = static_cast<int>(((rec >> 5) & 7u) | ((rec >> 10) & 0x38u) | ((rec >> 15) & 0x1C0u) | ((rec >> 20) & 0xE00u));
+                    else
+                        e = static_cast<int>((rec >> (12 + 10 * u)) & 1023u);
+                    strip_flush<TILE>(acc, wave, m, h, e, row0);
+                }
+            }
+        }
+    };
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+        step_barrier();
+        contract(2 * k);
+        contract(2 * k + 1);
+    }
+}
+
+template <int TILE>
+__device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64_t t0) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
+    const DmBlock b = load_block(A.blocks, blk);
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int groups = (A.nchan + 7) / 8;
+    // steps of two groups, in whole rounds of the load stages (the tables are padded)
+    const int K = ((groups + 1) / 2 + kStripStages - 1) / kStripStages * kStripStages;
+    for (int i = tid; i < strip_ring(TILE) / 16; i += kThreads) reinterpret_cast<u32x4*>(lds)[i] = u32x4{0u, 0u, 0u, 0u};
+    if (wave < kContract) {
+        if (__builtin_amdgcn_readfirstlane(b.cps) == 8)
+            strip_contract<TILE, 8>(A, b, lds, wave, lane, K);
+        else
+            strip_contract<TILE, 4>(A, b, lds, wave, lane, K);
+    } else {
+        if (t0 + b.rs_lo < 0 || t0 + b.rs_hi + 4 * kStripRowDwords > A.n_in16 || A.in_pitch > kStripMaxPitch)
+            strip_stage<TILE, true>(A, b, blk, t0, lds, wave - kContract, lane, K);
+        else
+            strip_stage<TILE, false>(A, b, blk, t0, lds, wave - kContract, lane, K);
+    }
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    __syncthreads();
+
+    const int32_t corr = 128 * 8 * groups;
+    const int32_t* acc_lds = reinterpret_cast<const int32_t*>(lds + kAcc0);
+#pragma unroll 1
+    for (int idx = tid; idx < TILE * 8; idx += kThreads) {   // 4 samples x 1 trial per item
+        const int d = idx & 31, tq = idx >> 5;
+        int32_t v[4];
+#pragma unroll
+        for (int jj = 0; jj < 4; ++jj) v[jj] = acc_lds[(4 * tq + jj) * 32 + d] + corr;
+        if (d < b.count) {
+            int32_t* orow = A.out + static_cast<int64_t>(b.first + d) * A.out_pitch;
+            const int64_t t = t0 + 4 * tq;
+            if (t + 4 <= A.n_out) {
+                *reinterpret_cast<u32x4*>(orow + t) = u32x4{static_cast<uint32_t>(v[0]), static_cast<uint32_t>(v[1]),
+                                                           static_cast<uint32_t>(v[2]), static_cast<uint32_t>(v[3])};
+            } else {
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj)
+                    if (t + jj < A.n_out) orow[t + jj] = v[jj];
+            }
+        }
+    }
+}
+
+__global__ __launch_bounds__(kThreads, 4) void dedisp_strip_kernel(DedispArgs a) {
+    const int bid = xcd_remap(blockIdx.x, gridDim.x);
+    dedisp_strip<kStripTile>(a, bid % a.nblk, static_cast<int64_t>(bid / a.nblk) * kStripTile);
+}
+
+__global__ __launch_bounds__(kThreads, 4) void dedisp_strip_batch_kernel(const DedispArgs* __restrict__ args,
+                                                                         const int64_t* __restrict__ item_begin, int nbeams,
+                                                                         int64_t total, unsigned long long* counter) {
+    batch_items(args, item_begin, nbeams, total, counter, [](const DedispArgs& a, int blk, int64_t tile) {
+        dedisp_strip<kStripTile>(a, blk, tile * kStripTile);
+    });
+}
+
+}  // namespace
+
+const DedispFn kStripKernel = dedisp_strip_kernel;
+const DedispBatchFn kStripBatchKernel = dedisp_strip_batch_kernel;
+
+}  // namespace aa

@@ -44,6 +44,8 @@ const DedispVariant kDedispVariants[kNumDedispVariants] = {
     {22, 8, 4, quad_lds_bytes(32), 7, 1024, 32, 0},   // 512 threads, 2 samples per lane
     {23, 16, 2, quad_lds_bytes(32), 7, 1024, 32, 0},  // 1024 threads, 1 sample per lane
     {24, 8, 4, quad_lds_bytes(16), 7, 512, 16, 0},    // 512 threads, 1 sample per lane
+    // matrix cores over 128-row strips, 32 trials per block, separate staging waves
+    {25, 16, 2, strip_lds_bytes(kStripTile), 8, kStripTile, 2, 0},   // 1024 threads
 };
 
 void free_tables(DedispTables& t) {
@@ -422,7 +424,203 @@ int build_quad_tables(const aa_plan_s* p, int tile, int chunks, std::vector<DmBl
     return AA_OK;
 }
 
+// Tables of the strip variant (layout 8, see aa_internal.h). A DM block is the longest
+// range of up to 32 trials (tried from 32 down) whose every substep has a residual range
+// below R and whose every run's spread of E is at most strip_spread(tile). A single trial
+// always qualifies (f = 0). Runs are greedy.
 namespace {
+
+struct StripRun {
+    int s0, s1;                // substeps [s0, s1)
+    int32_t emin, emax;        // over the block's trials
+};
+
+// Residual ranges of one DM block, per substep (cps channels) and trial.
+struct StripBlock {
+    int first, count, cps, nsub;
+    std::vector<int32_t> lo, hi;   // [nsub][count] min and max over the substep of f(d, c)
+};
+
+void strip_ranges(const aa_plan_s* p, int first, int count, int cps, StripBlock& b) {
+    const int nchan = p->nchan;
+    b.first = first;
+    b.count = count;
+    b.cps = cps;
+    b.nsub = (nchan + 7) / 8 * (8 / cps);   // whole steps: an empty last substep joins its run
+    b.lo.resize(static_cast<size_t>(b.nsub) * count);
+    b.hi.resize(static_cast<size_t>(b.nsub) * count);
+    const int32_t* ref = &p->shifts[static_cast<size_t>(first + count / 2) * nchan];
+    for (int i = 0; i < count; ++i) {
+        const int32_t* sd = &p->shifts[static_cast<size_t>(first + i) * nchan];
+        for (int s = 0; s < b.nsub; ++s) {
+            const int c0 = s * cps, c1 = std::min(c0 + cps, nchan);
+            int32_t l = INT32_MAX, h = INT32_MIN;
+            for (int c = c0; c < c1; ++c) {
+                const int32_t f = sd[c] - ref[c];
+                l = std::min(l, f);
+                h = std::max(h, f);
+            }
+            b.lo[static_cast<size_t>(s) * count + i] = l;
+            b.hi[static_cast<size_t>(s) * count + i] = h;
+        }
+    }
+}
+
+// Greedy runs; false if a substep or a run's spread of E breaks the limits.
+bool strip_runs(const StripBlock& b, int spread_max, std::vector<StripRun>& runs) {
+    const int R = 32 / b.cps, n = b.count;
+    runs.clear();
+    int32_t l[32], h[32];
+    for (int s = 0; s < b.nsub;) {
+        const int32_t* lo = &b.lo[static_cast<size_t>(s) * n];
+        const int32_t* hi = &b.hi[static_cast<size_t>(s) * n];
+        for (int i = 0; i < n; ++i) {
+            l[i] = lo[i];
+            h[i] = hi[i];
+            if (h[i] - l[i] > R - 1) return false;
+        }
+        int s1 = s + 1;
+        while (s1 < b.nsub) {
+            const int32_t* ln = &b.lo[static_cast<size_t>(s1) * n];
+            const int32_t* hn = &b.hi[static_cast<size_t>(s1) * n];
+            int32_t range = 0;
+            for (int i = 0; i < n; ++i) range = std::max(range, std::max(h[i], hn[i]) - std::min(l[i], ln[i]));
+            if (range > R - 1) break;
+            for (int i = 0; i < n; ++i) {
+                l[i] = std::min(l[i], ln[i]);
+                h[i] = std::max(h[i], hn[i]);
+            }
+            ++s1;
+        }
+        const int32_t emin = *std::min_element(l, l + n), emax = *std::max_element(l, l + n);
+        if (emax - emin > spread_max) return false;
+        runs.push_back(StripRun{s, s1, emin, emax});
+        s = s1;
+    }
+    return true;
+}
+
+// Estimated cycles of a block's work per time tile: see the cost rule at build_strip_tables.
+double strip_cost(const std::vector<StripRun>& runs, int cps, int tile) {
+    double c = 0.0;
+    for (const StripRun& r : runs) {
+        const int strips = (tile + (r.emax - r.emin) + kStripRows - 1) / kStripRows;
+        const double per_simd = (strips + 3) / 4;
+        c += (r.s1 - r.s0) * (cps == 8 ? 60.0 + 150.0 * per_simd : 40.0 + 150.0 * per_simd) + 280.0 * strips + 300.0;
+    }
+    return c;
+}
+
+}  // namespace
+
+int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBlock>& blocks, std::vector<int32_t>& rs,
+                       std::vector<uint32_t>& rec) {
+    if (tile % 32 || tile < 128 || strip_spread(tile) < 0 || (shape != 0 && shape != 4 && shape != 8))
+        return fail(AA_EINVAL, "strip tiling: bad tile or shape");
+    const int nchan = p->nchan, npad = strip_nchan_pad(nchan), K = npad / 8, Kinfo = (K + 63) / 64 * 64;
+    const size_t blk_dwords = static_cast<size_t>(K) * 64 + Kinfo;
+    blocks.clear();
+    rs.clear();
+    rec.clear();
+    StripBlock sb, best_sb;
+    std::vector<StripRun> runs, best_runs;
+    for (int d0 = 0; d0 < p->ndm;) {
+        // the longest block of each shape, then the cheaper one per trial
+        double best = -1.0;
+        for (int cps : {8, 4}) {
+            if (shape != 0 && cps != shape) continue;
+            int count = std::min(32, p->ndm - d0);
+            for (;;) {
+                strip_ranges(p, d0, count, cps, sb);
+                if (strip_runs(sb, strip_spread(tile), runs)) break;
+                if (count == 1) return fail(AA_EINVAL, "strip tiling: a single trial does not fit");
+                count -= count > 16 ? 4 : count > 8 ? 2 : 1;
+            }
+            const double cost = strip_cost(runs, cps, tile) / count;
+            if (best < 0.0 || cost < best) {
+                best = cost;
+                std::swap(best_sb, sb);
+                std::swap(best_runs, runs);
+            }
+        }
+        const StripBlock& b = best_sb;
+        const int count = b.count, cps = b.cps, R = 32 / cps;
+        const size_t at = rec.size(), rat = rs.size();
+        rec.resize(at + blk_dwords, 0u);
+        rs.resize(rat + npad, 0);
+        uint32_t* info = &rec[at + static_cast<size_t>(K) * 64];
+        const int32_t* ref = &p->shifts[static_cast<size_t>(d0 + count / 2) * nchan];
+        int32_t E[32];
+        for (const StripRun& r : best_runs) {
+            for (int i = 0; i < count; ++i) {
+                E[i] = INT32_MAX;
+                for (int s = r.s0; s < r.s1; ++s) E[i] = std::min(E[i], b.lo[static_cast<size_t>(s) * count + i]);
+            }
+            const uint32_t emax = static_cast<uint32_t>(r.emax - r.emin);
+            const uint32_t strips = (static_cast<uint32_t>(tile) + emax + kStripRows - 1) / kStripRows;
+            const bool wide = tile + static_cast<int>(emax) + R - 1 > kStripNarrowBytes;
+            for (int s = r.s0; s < r.s1; ++s) {
+                const int k = s * cps / 8, u = cps == 8 ? 0 : s & 1;
+                uint32_t& f = info[k];
+                f |= (s + 1 == r.s1 ? 1u : 0u) << u | (strips - 1) << (2 + 4 * u) | emax << (10 + 10 * u);
+                if (wide) f |= 1u << 30;
+                uint32_t* rk = &rec[at + static_cast<size_t>(k) * 64];
+                for (int c = s * cps; c < std::min(s * cps + cps, nchan); ++c) rs[rat + c] = ref[c] + r.emin;
+                for (int i = 0; i < count; ++i) {
+                    const int32_t* sd = &p->shifts[static_cast<size_t>(d0 + i) * nchan];
+                    const uint32_t e = static_cast<uint32_t>(E[i] - r.emin);
+                    for (int h = 0; h < 2; ++h) {
+                        uint32_t v = 0;
+                        if (cps == 8) {
+                            for (int j = 0; j < 4; ++j) {
+                                const int c = 8 * k + 4 * h + j;
+                                const uint32_t res = c < nchan ? static_cast<uint32_t>(sd[c] - ref[c] - E[i]) : 0u;
+                                v |= (8u * res | ((e >> (3 * j)) & 7u) << 5) << (8 * j);
+                            }
+                        } else {
+                            for (int j = 0; j < 2; ++j) {
+                                const int c = 8 * k + 4 * u + 2 * h + j;
+                                const uint32_t res = c < nchan ? static_cast<uint32_t>(sd[c] - ref[c] - E[i]) : 0u;
+                                v |= res << (3 * (2 * u + j));
+                            }
+                            v |= e << (12 + 10 * u);
+                        }
+                        rk[32 * h + i] |= v;
+                    }
+                }
+            }
+        }
+        if (cps == 8)
+            for (int k = 0; k < K; ++k) info[k] |= (info[k] & 1u) << 1;
+        const int32_t* r0 = &rs[rat];
+        DmBlock blk{d0, count, 0, *std::min_element(r0, r0 + npad), *std::max_element(r0, r0 + npad), cps,
+                    static_cast<int32_t>(at / 64)};
+        blocks.push_back(blk);
+        d0 += count;
+    }
+    return AA_OK;
+}
+
+namespace {
+int prepare_strip(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
+    std::vector<DmBlock> blocks;
+    std::vector<int32_t> rs;
+    std::vector<uint32_t> rec;
+    const int rc0 = build_strip_tables(p, V.tile, 0, blocks, rs, rec);
+    if (rc0 != AA_OK) return rc0;
+    t.bd = 32;
+    t.nchan_pad = strip_nchan_pad(p->nchan);
+    t.max_row = 0;
+    t.blocks = blocks;
+    if (p->device >= 0) {
+                int rc = upload(&t.d_blocks, blocks);
+        if (rc == AA_OK) rc = upload(&t.d_base, rs);
+        if (rc == AA_OK) rc = upload(reinterpret_cast<uint32_t**>(&t.d_offs), rec);
+        if (rc != AA_OK) return rc;
+    }
+    return AA_OK;
+}
+
 int prepare_quad(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     std::vector<DmBlock> blocks;
     std::vector<int32_t> rec;
@@ -486,7 +684,8 @@ int prepare_variant(aa_plan_s* p, int v) {
     if (V.layout >= 4) {
         DedispTables t;
         t.variant = v;
-        const int rc = V.layout == 7 ? prepare_quad(p, V, t) : prepare_mfma(p, V, t);
+        const int rc = V.layout == 8 ? prepare_strip(p, V, t)
+                       : V.layout == 7 ? prepare_quad(p, V, t) : prepare_mfma(p, V, t);
         if (rc != AA_OK) {
             free_tables(t);
             return rc;

@@ -140,21 +140,19 @@ constexpr int quad_lds_bytes(int chunks) { return 2 * chunks * 1024; }
 //     R = 8: bits 3 i .. 3 i + 2 hold r of channel 4 (i / 2) + 2 h + i % 2 (substep i / 2);
 //            bits 12-21 and 22-31 hold e of the runs of substeps 0 and 1
 //   info: bit 0 / 1: substep 0 / 1 is its run's last (bit 1 copies bit 0 for R = 4);
-//     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e;
-//     bit 30: a row of the group needs more than kStripNarrowBytes staged bytes
+//     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e
 constexpr int kStripTile = 832;
 constexpr int kStripRows = 128;
 constexpr int kStripWaves = 12;          // contracting waves, one strip each
 constexpr int kStripStages = 2;          // load stages of the staging waves
-constexpr int kStripNarrowBytes = 1016;  // staged bytes of a row in two passes of 127 dwords
-constexpr int kStripWideBytes = 1524;    // and in three
-constexpr int kStripRowDwords = 388;     // LDS entries per row: 12 strips, 3 to read past, a spare one
+constexpr int kStripNarrowBytes = 1024;  // staged bytes of a row in two passes of 128 dwords
+constexpr int kStripWideBytes = 1536;    // and in three
+constexpr int kStripRowDwords = 388;     // LDS entries per row: 12 strips and 4 to read past
 constexpr uint32_t kStripNoRow = 0x7fff0000u;           // row offset (and end) of a unit's load range
 constexpr int64_t kStripMaxPitch = int64_t{1} << 26;    // 16 pitches and a row start stay below it
-// channels covered by the tables: whole rounds of kStripStages steps of two groups, and the
-// group that the last step reads ahead
+// channels covered by the tables: whole rounds of kStripStages steps of two groups
 constexpr int strip_nchan_pad(int nchan) {
-    return 16 * kStripStages * (((nchan + 7) / 8 + 2 * kStripStages) / (2 * kStripStages)) + 16 * kStripStages;
+    return (nchan + 16 * kStripStages - 1) / (16 * kStripStages) * (16 * kStripStages);
 }
 constexpr int strip_lds_bytes(int tile) { return (tile + 2) * 32 * 4 + 4 * (8 * kStripRowDwords * 4 + 256); }
 // largest e whose rows fit the strips, their window reads the staged bytes, and e its field
@@ -179,7 +177,8 @@ constexpr int kSpsRows = 8;
 struct DmBlock {
     int32_t first;   // first DM trial of the block
     int32_t count;   // trials in the block (<= waves * dpw)
-    int32_t row;     // LDS row length (bytes) the block needs, multiple of 16 (layouts 0-3)
+    int32_t row;     // LDS row length (bytes) the block needs, multiple of 16 (layouts 0-3);
+                     // layout 8: largest staged row length (bytes) of its runs
     int32_t rs_lo;   // layouts 4-6, 8: smallest and largest staged-row start over the block's
     int32_t rs_hi;   // channels, relative to the time tile (0 for the other layouts)
     int32_t cps;     // layouts 4-6, 8: channels per matrix step of this block (4 or 8)

@@ -15,9 +15,10 @@
 //    16-byte LDS entry per dword of time, with the sign flip (XOR 0x80) done once per staged
 //    dword. So the operand reads are wide LDS reads at constant offsets: no window
 //    addresses, phases or sign flips remain in the matrix loop.
-//  * A step is two groups of 8 channels and one barrier. The ring holds four groups: in step
-//    k the contracting waves use groups 2 k and 2 k + 1 and read the operands of 2 k + 1 and
-//    2 k + 2, while the staging waves fill the places of 2 k + 3 and 2 k + 4.
+//  * A step is two groups of 8 channels and one barrier. The LDS ring holds two steps: in
+//    step k the contracting waves run the matrix ops of step k on operands already in
+//    registers and read those of step k + 1, while the staging waves store step k + 2. So no
+//    LDS latency is waited for within a step.
 #include "dedisp_device.h"
 
 namespace aa {
@@ -63,31 +64,28 @@ __device__ __forceinline__ void strip_flush(i32x16 (&acc)[4], int q, int m, int 
     for (int j = 0; j < 4; ++j) acc[j] = i32x16{};
 }
 
-// The staging waves. Unit n is the pair of groups 2 n - 1 and 2 n (16 channels, four quads);
-// wave p stages quad p of every unit, PASSES loads of two dwords per lane and row. A lane
-// needs its successor's first dword to align its own two, so a pass yields 127 dwords.
+// The staging waves. Wave p stages quad p of the four of every step, PASSES loads of two dwords per lane and row, straight
+// from the rows' byte-exact starts. Unaligned, the loads run at half of the L1 rate (16
+// cycles per 512-byte load instruction, measured), but aligned ones would need three more
+// vector operations per dword, and the staging waves' instruction stream is what the step
+// waits for.
 // EDGE: rows of the tile may start before sample 0 or run past the input's end (or row
 // offsets do not fit 31 bits).
-template <int TILE, bool EDGE>
+template <int TILE, int PASSES, bool EDGE>
 __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& b, int blk, int64_t t0, uint8_t* lds,
                                             int p, int lane, int K) {
-    constexpr int D = kStripStages, PASSES = 3, VALID = 127;
+    constexpr int D = kStripStages;
     const int64_t pitch = A.in_pitch;
     const uint32_t* const recs = reinterpret_cast<const uint32_t*>(A.offs) + static_cast<int64_t>(b.rec256) * 64;
-    const uint32_t* const infos = recs + static_cast<int64_t>(A.nchan_pad >> 3) * 64;
     const int32_t* const rsv = A.base + static_cast<int64_t>(blk) * A.nchan_pad;
-    // unit n's first channel is 16 n - 8; this wave's quad
-    const int c0 = 4 * p - 8;
-    const int group = p >> 1;                         // of the unit
+    const int group = p >> 1;                         // of the step
     int wdst[PASSES][2];
 #pragma unroll
     for (int s = 0; s < PASSES; ++s)
 #pragma unroll
-        for (int l = 0; l < 2; ++l)   // (a pass's last dword lacks its successor: into a spare entry)
-            wdst[s][l] = strip_ring(TILE) + (p & 1) * kQuadBytes +
-                         entry_at(2 * lane + l < VALID ? VALID * s + 2 * lane + l : kStripRowDwords - 1);
+        for (int l = 0; l < 2; ++l) wdst[s][l] = strip_ring(TILE) + (p & 1) * kQuadBytes + entry_at(128 * s + 2 * lane + l);
 
-    // One buffer resource per unit, based 16 bytes before its first row at the time tile; a
+    // One buffer resource per step, based 16 bytes before its first row at the time tile; a
     // row is reached through the scalar offset, which the range check counts: channels that
     // do not exist carry an offset beyond the range and read zeros (they enter the sums as
     // -128 per channel like every zero byte, and the final correction counts them). An EDGE
@@ -95,51 +93,40 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
     // would read outside moves to the nearest dword inside, and its bytes are shifted back to
     // their places when they are written to LDS (bytes from outside only reach outputs that
     // are not stored).
-    const uint8_t* sbase = EDGE ? A.in + c0 * pitch : A.in + t0 - 16 - 8 * pitch;
-    int nunit = 0;             // next unit to load
-    // per-unit tables, 64 units at a time, lane l holding unit 64 n + l
-    u32x4 off_tab{};           // offsets of the quad's rows from the unit's base
-    uint32_t info_tab = 0;     // infos of the wave's group
+    const uint8_t* sbase = EDGE ? A.in + 4 * p * pitch : A.in + t0 - 16;
+    int nstep = 0;             // next step to load
+    // per-step tables, 64 steps at a time, lane l holding step 64 n + l
+    u32x4 off_tab{};           // offsets of the quad's rows from the step's base
     uint32_t st[D][PASSES][2][4];   // dwords in flight, [stage][pass][dword][channel]
-    uint32_t st_rec[D];        // record dwords in flight (waves 0 and 1: of group `p` of the unit)
-    uint32_t st_phase[D][4];   // bytes of each row before its start in its first dword
+    uint32_t st_rec[D];        // record dwords in flight (waves 0 and 1: of group `p` of the step)
     int st_lo[D][4], st_hi[D][4];   // EDGE: bounds of each row's byte positions
     const __amdgpu_buffer_rsrc_t rec_rs = __builtin_amdgcn_make_buffer_rsrc(
         const_cast<uint32_t*>(recs), 0, 256 * (A.nchan_pad >> 3), kRawBufferFlags);
     auto issue = [&](int s) {
-        if ((nunit & 63) == 0) {
-            const int c = 16 * (nunit + lane) + c0;
-            const bool in = c >= 0 && c < A.nchan_pad;
-            off_tab = in ? *reinterpret_cast<const u32x4*>(rsv + c) : u32x4{0u, 0u, 0u, 0u};
-            info_tab = in ? infos[2 * (nunit + lane) - 1 + group] : 0u;
+        if ((nstep & 63) == 0) {
+            const int c = 16 * (nstep + lane) + 4 * p;
+            off_tab = c < A.nchan_pad ? *reinterpret_cast<const u32x4*>(rsv + c) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
                 if constexpr (!EDGE) off_tab[i] += 16u + static_cast<uint32_t>((4 * p + i) * pitch);
-                if (c < 0 || c + i >= A.nchan) off_tab[i] = kStripNoRow;
+                if (c + i >= A.nchan) off_tab[i] = kStripNoRow;
             }
-            // wait for the tables here, so that the units that do not load them need no wait
-            asm volatile("" : "+v"(off_tab), "+v"(info_tab));
+            // wait for the tables here, so that the steps that do not load them need no wait
+            asm volatile("" : "+v"(off_tab));
         }
-        const int sl = nunit & 63;
-        const bool wide = ((__builtin_amdgcn_readlane(static_cast<int>(info_tab), sl) >> 30) & 1) != 0;
+        const int sl = nstep & 63;
         uint32_t so[4];
 #pragma unroll
         for (int i = 0; i < 4; ++i) so[i] = static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(off_tab[i]), sl));
         const int voff = 8 * lane;
         if constexpr (!EDGE) {
-            // (the last pass of a narrow group loads an empty range)
             const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
                 const_cast<uint8_t*>(sbase), 0, static_cast<int>(kStripNoRow), kRawBufferFlags);
-            const __amdgpu_buffer_rsrc_t rw = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<uint8_t*>(sbase), 0, wide ? static_cast<int>(kStripNoRow) : 0, kRawBufferFlags);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) st_phase[s][i] = so[i] & 3u;
 #pragma unroll
             for (int q = 0; q < PASSES; ++q)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const auto x = __builtin_amdgcn_raw_buffer_load_b64(q == PASSES - 1 ? rw : rs, voff + 4 * VALID * q,
-                                                                        so[i] & ~3u, 0);
+                    const auto x = __builtin_amdgcn_raw_buffer_load_b64(rs, voff + 512 * q, so[i], 0);
                     st[s][q][0][i] = x[0];
                     st[s][q][1][i] = x[1];
                 }
@@ -160,16 +147,16 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
 #pragma unroll
                     for (int l = 0; l < 2; ++l)
                         st[s][q][l][i] = __builtin_amdgcn_raw_buffer_load_b32(
-                            rs, min(max(voff + 4 * (VALID * q + l), lo), hi) - lo, 0, 0);
+                            rs, min(max(voff + 4 * (128 * q + l), lo), hi) - lo, 0, 0);
             }
         }
-        st_rec[s] = __builtin_amdgcn_raw_buffer_load_b32(rec_rs, 4 * lane, 256 * (2 * nunit - 1 + (p & 1)), 0);
-        ++nunit;
+        st_rec[s] = __builtin_amdgcn_raw_buffer_load_b32(rec_rs, 4 * lane, 256 * (2 * nstep + (p & 1)), 0);
+        ++nstep;
         sbase += 16 * pitch;
     };
-    // unit n from stage s into its places of the ring (group 2 n - 1 at place (2 n) % 4)
+    // step n from stage s into its half of the ring
     auto write = [&](int s, int n) {
-        uint8_t* const dst = lds + (((2 * n) & 3) + group) * kGroupBytes;
+        uint8_t* const dst = lds + (2 * (n & 1) + group) * kGroupBytes;
 #pragma unroll
         for (int q = 0; q < PASSES; ++q)
 #pragma unroll
@@ -178,14 +165,8 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     uint32_t v = st[s][q][l][i];
-                    if constexpr (!EDGE) {
-                        // the row's bytes start `phase` bytes into the loaded dwords
-                        const uint32_t next = l == 0 ? st[s][q][1][i]
-                                                     : static_cast<uint32_t>(__builtin_amdgcn_update_dpp(
-                                                           0, static_cast<int>(st[s][q][0][i]), 0x130, 0xf, 0xf, true));
-                        v = __builtin_amdgcn_alignbyte(next, v, st_phase[s][i]);
-                    } else {
-                        const int want = 8 * lane + 4 * (VALID * q + l);
+                    if constexpr (EDGE) {
+                        const int want = 8 * lane + 4 * (128 * q + l);
                         const int d = want - min(max(want, st_lo[s][i]), st_hi[s][i]);
                         v = d > 0 ? (d < 4 ? v >> (8 * d) : 0u) : d < 0 ? (d > -4 ? v << (-8 * d) : 0u) : v;
                     }
@@ -194,7 +175,7 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
                 *reinterpret_cast<u32x4*>(dst + wdst[q][l]) = o;
             }
         if (p < 2)
-            *reinterpret_cast<uint32_t*>(lds + strip_recs(TILE) + 256 * (((2 * n) & 3) + p) + 4 * lane) = st_rec[s];
+            *reinterpret_cast<uint32_t*>(lds + strip_recs(TILE) + 256 * (2 * (n & 1) + p) + 4 * lane) = st_rec[s];
     };
 
 #pragma unroll
@@ -206,8 +187,8 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
     step_barrier();
     // (the loop's own waits are counted only if nothing is in flight where it is entered)
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-    // whole rounds of D units, so that the loop has one exit: the waits for a stage's loads
-    // are counted over the loads issued after it on every path, and an exit per unit would
+    // whole rounds of D steps, so that the loop has one exit: the waits for a stage's loads
+    // are counted over the loads issued after it on every path, and an exit per step would
     // join states in which fewer are
     int k = 0;
     do {
@@ -233,23 +214,23 @@ __device__ __forceinline__ void strip_contract(const DedispArgs& A, const DmBloc
         reinterpret_cast<uintptr_t>((__attribute__((address_space(3))) uint8_t*)(lds + kAcc0)));
     const uint32_t* const infos = reinterpret_cast<const uint32_t*>(A.offs) + static_cast<int64_t>(b.rec256) * 64 +
                                   static_cast<int64_t>(A.nchan_pad >> 3) * 64;
-    const int ngroups = 2 * K;
-
-    // operand dwords of the next group and its record
-    uint32_t a[CPS == 8 ? 8 : 12], rec_next = 0;
+    // operand dwords of the step's two groups, and their records
+    constexpr int NA = CPS == 8 ? 8 : 12;
+    uint32_t a[2][NA], rec[2];
     const uint8_t* rsrc[NE];
 #pragma unroll
     for (int i = 0; i < NE; ++i)
         rsrc[i] = lds + strip_ring(TILE) + (CPS == 8 ? h * kQuadBytes : 8 * h) + entry_at(32 * wave + m + i);
-    auto read = [&](int g) {
-        const int off = ((g + 1) & 3) * kGroupBytes;
-        rec_next = *reinterpret_cast<const uint32_t*>(lds + strip_recs(TILE) + 256 * ((g + 1) & 3) + 4 * lane);
+    const uint8_t* const recp = lds + strip_recs(TILE) + 4 * lane;
+    auto read = [&](int k, int gi) {
+        const int place = 2 * (k & 1) + gi, off = place * kGroupBytes;
+        rec[gi] = *reinterpret_cast<const uint32_t*>(recp + 256 * place);
         if constexpr (CPS == 8) {
 #pragma unroll
             for (int i = 0; i < 2; ++i) {
                 const u32x4 x = *reinterpret_cast<const u32x4*>(rsrc[i] + off);
 #pragma unroll
-                for (int c = 0; c < 4; ++c) a[4 * i + c] = x[c];
+                for (int c = 0; c < 4; ++c) a[gi][4 * i + c] = x[c];
             }
         } else {
 #pragma unroll
@@ -257,87 +238,88 @@ __device__ __forceinline__ void strip_contract(const DedispArgs& A, const DmBloc
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const u32x2 x = *reinterpret_cast<const u32x2*>(rsrc[i] + off + u * kQuadBytes);
-                    a[6 * u + 2 * i] = x[0];
-                    a[6 * u + 2 * i + 1] = x[1];
+                    a[gi][6 * u + 2 * i] = x[0];
+                    a[gi][6 * u + 2 * i + 1] = x[1];
                 }
         }
     };
-    uint32_t info_tab = infos[min(lane, ngroups - 1)];   // lane l: group 64 n + l
-    auto info_of = [&](int g) {
-        if ((g & 63) == 0) {
-            info_tab = infos[min(g + lane, ngroups - 1)];
+    // infos of the steps (the low 10 bits of both groups'), lane l: step 64 n + l
+    uint32_t info_tab = 0;
+    auto info_of = [&](int k) {
+        if ((k & 63) == 0) {
+            const int g = 2 * min(k + lane, K - 1);
+            info_tab = (infos[g] & 1023u) | (infos[g + 1] & 1023u) << 10;
             asm volatile("" : "+v"(info_tab));
         }
-        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(info_tab), g & 63));
+        return static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(info_tab), k & 63));
     };
-    auto strips = [](uint32_t info, int u) { return static_cast<int>((info >> (2 + 4 * u)) & 15u) + 1; };
-    auto strips_any = [&](uint32_t info) { return NSUB == 1 ? strips(info, 0) : max(strips(info, 0), strips(info, 1)); };
+    auto strips = [](uint32_t info, int gi, int u) { return static_cast<int>((info >> (10 * gi + 2 + 4 * u)) & 15u) + 1; };
+    auto strips_any = [&](uint32_t info, int gi) {
+        return NSUB == 1 ? strips(info, gi, 0) : max(strips(info, gi, 0), strips(info, gi, 1));
+    };
 
     i32x16 acc[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = i32x16{};
     step_barrier();
     uint32_t info1 = info_of(0);
-    read(0);
-
-    // group g: windows from the operands read one group ahead, the next group's reads, matrix ops
-    auto contract = [&](int g) {
-        const uint32_t info = info1, rec = rec_next;
-        info1 = info_of(g + 1);
+    read(0, 0);
+    read(0, 1);
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+        const uint32_t info = info1;
+        info1 = info_of(k + 1);
+        step_barrier();
 #pragma unroll
-        for (int u = 0; u < NSUB; ++u) {
-            const bool on = wave < strips(info, u);
-            i32x4 w[4], B;
-            if (on) {
+        for (int gi = 0; gi < 2; ++gi) {
+            const uint32_t r0 = rec[gi];
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
+            for (int u = 0; u < NSUB; ++u) {
+                const bool on = wave < strips(info, gi, u);
+                if (on) {
+                    i32x4 B;
                     if constexpr (CPS == 8) {
 #pragma unroll
-                        for (int i = 0; i < 4; ++i)
-                            w[j][i] = static_cast<int32_t>(j == 0 ? a[i] : __builtin_amdgcn_alignbyte(a[4 + i], a[i], j));
+                        for (int i = 0; i < 4; ++i) B[i] = static_cast<int32_t>(1u << ((r0 >> (8 * i)) & 31u));
                     } else {
 #pragma unroll
-                        for (int i = 0; i < 2; ++i) {
-                            const uint32_t x0 = a[6 * u + i], x1 = a[6 * u + 2 + i], x2 = a[6 * u + 4 + i];
-                            w[j][2 * i] = static_cast<int32_t>(j == 0 ? x0 : __builtin_amdgcn_alignbyte(x1, x0, j));
-                            w[j][2 * i + 1] = static_cast<int32_t>(j == 0 ? x1 : __builtin_amdgcn_alignbyte(x2, x1, j));
+                        for (int j = 0; j < 2; ++j) {
+                            const uint32_t r = (r0 >> (3 * (2 * u + j))) & 7u;
+                            const uint32_t one = 1u << (8u * (r & 3u));
+                            B[2 * j] = static_cast<int32_t>(r < 4u ? one : 0u);
+                            B[2 * j + 1] = static_cast<int32_t>(r < 4u ? 0u : one);
                         }
                     }
-                }
-                if constexpr (CPS == 8) {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) B[i] = static_cast<int32_t>(1u << ((rec >> (8 * i)) & 31u));
-                } else {
+                    for (int j = 0; j < 4; ++j) {
+                        i32x4 w;
+                        if constexpr (CPS == 8) {
 #pragma unroll
-                    for (int j = 0; j < 2; ++j) {
-                        const uint32_t r = (rec >> (3 * (2 * u + j))) & 7u;
-                        const uint32_t one = 1u << (8u * (r & 3u));
-                        B[2 * j] = static_cast<int32_t>(r < 4u ? one : 0u);
-                        B[2 * j + 1] = static_cast<int32_t>(r < 4u ? 0u : one);
+                            for (int i = 0; i < 4; ++i)
+                                w[i] = static_cast<int32_t>(j == 0 ? a[gi][i] : __builtin_amdgcn_alignbyte(a[gi][4 + i], a[gi][i], j));
+                        } else {
+#pragma unroll
+                            for (int i = 0; i < 2; ++i) {
+                                const uint32_t x0 = a[gi][6 * u + i], x1 = a[gi][6 * u + 2 + i], x2 = a[gi][6 * u + 4 + i];
+                                w[2 * i] = static_cast<int32_t>(j == 0 ? x0 : __builtin_amdgcn_alignbyte(x1, x0, j));
+                                w[2 * i + 1] = static_cast<int32_t>(j == 0 ? x1 : __builtin_amdgcn_alignbyte(x2, x1, j));
+                            }
+                        }
+                        acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w, B, acc[j], 0, 0, 0);
                     }
                 }
-            }
-            if (u == NSUB - 1 && wave < strips_any(info1)) read(g + 1);
-            if (on) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_i32_32x32x32_i8(w[j], B, acc[j], 0, 0, 0);
-                if ((info >> u) & 1u) {
+                if (u == NSUB - 1 && wave < strips_any(info1, gi)) read(k + 1, gi);
+                if (on && ((info >> (10 * gi + u)) & 1u)) {
                     // the run ends here: add its strip into the accumulator tile
                     int e;
                     if constexpr (CPS == 8)
-                        e = static_cast<int>(((rec >> 5) & 7u) | ((rec >> 10) & 0x38u) | ((rec >> 15) & 0x1C0u) | ((rec >> 20) & 0xE00u));
+                        e = static_cast<int>(((r0 >> 5) & 7u) | ((r0 >> 10) & 0x38u) | ((r0 >> 15) & 0x1C0u) | ((r0 >> 20) & 0xE00u));
                     else
-                        e = static_cast<int>((rec >> (12 + 10 * u)) & 1023u);
+                        e = static_cast<int>((r0 >> (12 + 10 * u)) & 1023u);
                     strip_flush<TILE>(acc, wave, m, h, e, row0);
                 }
             }
         }
-    };
-#pragma unroll 1
-    for (int k = 0; k < K; ++k) {
-        step_barrier();
-        contract(2 * k);
-        contract(2 * k + 1);
     }
 }
 
@@ -351,16 +333,20 @@ __device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64
     // steps of two groups, in whole rounds of the load stages (the tables are padded)
     const int K = ((groups + 1) / 2 + kStripStages - 1) / kStripStages * kStripStages;
     for (int i = tid; i < strip_ring(TILE) / 16; i += kThreads) reinterpret_cast<u32x4*>(lds)[i] = u32x4{0u, 0u, 0u, 0u};
-    if (wave < kContract) {
+    // the staging waves are the oldest of their SIMDs, which win issue
+    if (wave >= kStage) {
         if (__builtin_amdgcn_readfirstlane(b.cps) == 8)
-            strip_contract<TILE, 8>(A, b, lds, wave, lane, K);
+            strip_contract<TILE, 8>(A, b, lds, wave - kStage, lane, K);
         else
-            strip_contract<TILE, 4>(A, b, lds, wave, lane, K);
+            strip_contract<TILE, 4>(A, b, lds, wave - kStage, lane, K);
     } else {
-        if (t0 + b.rs_lo < 0 || t0 + b.rs_hi + 4 * kStripRowDwords > A.n_in16 || A.in_pitch > kStripMaxPitch)
-            strip_stage<TILE, true>(A, b, blk, t0, lds, wave - kContract, lane, K);
+        // (b.row: staged bytes per row)
+        if (t0 + b.rs_lo < 0 || t0 + b.rs_hi + kStripWideBytes > A.n_in16 || A.in_pitch > kStripMaxPitch)
+            strip_stage<TILE, 3, true>(A, b, blk, t0, lds, wave, lane, K);
+        else if (__builtin_amdgcn_readfirstlane(b.row) <= kStripNarrowBytes)
+            strip_stage<TILE, 2, false>(A, b, blk, t0, lds, wave, lane, K);
         else
-            strip_stage<TILE, false>(A, b, blk, t0, lds, wave - kContract, lane, K);
+            strip_stage<TILE, 3, false>(A, b, blk, t0, lds, wave, lane, K);
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     __syncthreads();

@@ -549,6 +549,7 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
         rec.resize(at + blk_dwords, 0u);
         rs.resize(rat + npad, 0);
         uint32_t* info = &rec[at + static_cast<size_t>(K) * 64];
+        int row_bytes = 0;
         const int32_t* ref = &p->shifts[static_cast<size_t>(d0 + count / 2) * nchan];
         int32_t E[32];
         for (const StripRun& r : best_runs) {
@@ -558,12 +559,11 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
             }
             const uint32_t emax = static_cast<uint32_t>(r.emax - r.emin);
             const uint32_t strips = (static_cast<uint32_t>(tile) + emax + kStripRows - 1) / kStripRows;
-            const bool wide = tile + static_cast<int>(emax) + R - 1 > kStripNarrowBytes;
+            row_bytes = std::max(row_bytes, tile + static_cast<int>(emax) + R - 1);
             for (int s = r.s0; s < r.s1; ++s) {
                 const int k = s * cps / 8, u = cps == 8 ? 0 : s & 1;
                 uint32_t& f = info[k];
                 f |= (s + 1 == r.s1 ? 1u : 0u) << u | (strips - 1) << (2 + 4 * u) | emax << (10 + 10 * u);
-                if (wide) f |= 1u << 30;
                 uint32_t* rk = &rec[at + static_cast<size_t>(k) * 64];
                 for (int c = s * cps; c < std::min(s * cps + cps, nchan); ++c) rs[rat + c] = ref[c] + r.emin;
                 for (int i = 0; i < count; ++i) {
@@ -593,7 +593,7 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
         if (cps == 8)
             for (int k = 0; k < K; ++k) info[k] |= (info[k] & 1u) << 1;
         const int32_t* r0 = &rs[rat];
-        DmBlock blk{d0, count, 0, *std::min_element(r0, r0 + npad), *std::max_element(r0, r0 + npad), cps,
+        DmBlock blk{d0, count, row_bytes, *std::min_element(r0, r0 + npad), *std::max_element(r0, r0 + npad), cps,
                     static_cast<int32_t>(at / 64)};
         blocks.push_back(blk);
         d0 += count;

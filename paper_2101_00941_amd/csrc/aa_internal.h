@@ -127,33 +127,34 @@ constexpr int quad_lds_bytes(int chunks) { return 2 * chunks * 1024; }
 // so that residuals drift over at most half a block and a channel block holds about twice
 // the channels. A group is 8 consecutive channels in two quads of 4; a substep is one matrix
 // op's channels (8 for R = 4 residuals, 4 for R = 8), and channel blocks ("runs") end
-// between substeps. Row c is staged from its exact start rs[c] = base[c] + min E (may be
-// negative down to 1 - R, or exceed the input's end, where only unstored outputs read).
+// between substeps. Trial d's tile is skewed: it covers the outputs t0 + skew[d] + [0, tile),
+// with skew[d] (a multiple of 4) minus the middle of E[d]'s range over the channels. So
+// E'[d] = E[d] + skew[d] swings around zero, and its spread over the block, which costs rows
+// of t' beyond the tile, is half of E's. Row c is staged from its exact start
+// rs[c] = base[c] + min E' (it may be negative, or exceed the input's end, where only unstored
+// outputs read); e[d] = E'[d] - min E'.
 // A strip is 128 consecutive rows of t'; a run needs ceil((tile + max e) / 128) of them.
 // Tables:
 //   base: rs[nblk][nchan_pad], 0 for channels past nchan
 //   records (d_offs): per block nchan_pad / 8 group records of 64 dwords, one per lane
 //     (m = lane & 31 the trial, h = lane >> 5 the half), then as many info dwords, padded to
-//     a multiple of 64:
+//     a multiple of 64, then skew[32] padded to 64 dwords:
 //     R = 4: byte i holds 8 r of channel 4 h + i in its low 5 bits; the top 3 bits of the
 //            four bytes hold e (3 bits each, byte 0 lowest)
 //     R = 8: bits 3 i .. 3 i + 2 hold r of channel 4 (i / 2) + 2 h + i % 2 (substep i / 2);
 //            bits 12-21 and 22-31 hold e of the runs of substeps 0 and 1
 //   info: bit 0 / 1: substep 0 / 1 is its run's last (bit 1 copies bit 0 for R = 4);
 //     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e
-constexpr int kStripTile = 832;
+constexpr int kStripTile = 864;
+constexpr int kStripBias = 1024;         // bytes before the time tile that row starts stay within
 constexpr int kStripRows = 128;
 constexpr int kStripWaves = 12;          // contracting waves, one strip each
-constexpr int kStripStages = 2;          // load stages of the staging waves
 constexpr int kStripNarrowBytes = 1024;  // staged bytes of a row in two passes of 128 dwords
 constexpr int kStripWideBytes = 1536;    // and in three
 constexpr int kStripRowDwords = 388;     // LDS entries per row: 12 strips and 4 to read past
 constexpr uint32_t kStripNoRow = 0x7fff0000u;           // row offset (and end) of a unit's load range
 constexpr int64_t kStripMaxPitch = int64_t{1} << 26;    // 16 pitches and a row start stay below it
-// channels covered by the tables: whole rounds of kStripStages steps of two groups
-constexpr int strip_nchan_pad(int nchan) {
-    return (nchan + 16 * kStripStages - 1) / (16 * kStripStages) * (16 * kStripStages);
-}
+constexpr int strip_nchan_pad(int nchan) { return (nchan + 15) / 16 * 16; }   // whole steps of two groups
 constexpr int strip_lds_bytes(int tile) { return (tile + 2) * 32 * 4 + 4 * (8 * kStripRowDwords * 4 + 256); }
 // largest e whose rows fit the strips, their window reads the staged bytes, and e its field
 constexpr int strip_spread(int tile) {
@@ -183,6 +184,8 @@ struct DmBlock {
     int32_t rs_hi;   // channels, relative to the time tile (0 for the other layouts)
     int32_t cps;     // layouts 4-6, 8: channels per matrix step of this block (4 or 8)
     int32_t rec256;  // layouts 4-8: offset of the block's records in 256-byte units
+    int32_t lead = 0;    // layout 8: largest skew (time tile i starts at sample i * tile - lead)
+    int32_t span = 0;    // layout 8: largest minus smallest skew
 };
 
 // Per-variant tables. For block b and channel c:
@@ -200,6 +203,7 @@ struct DedispTables {
     int32_t* d_offs = nullptr;
     uint8_t* d_pad = nullptr;        // layouts 4-6: one staged row of 0x80 bytes (padded channels)
     int split = -1;                  // layout 6: first trial of the 4-channel blocks
+    int32_t span = 0;                // layout 8: largest span of a block's skews
 };
 
 // Arguments of one dedispersion launch (one beam), passed by value or from a device table.

@@ -1040,7 +1040,7 @@ DedispArgs dedisp_args(const aa_plan_s* p, int variant, const uint8_t* d_in, int
     a.row = T.max_row;
     const int tile = kDedispVariants[variant].tile;
     a.tile = tile;
-    a.ntile = (a.n_out + tile - 1) / tile;
+    a.ntile = (a.n_out + T.span + tile - 1) / tile;   // (layout 8: skewed tiles reach past both ends)
     a.pad = T.d_pad;
     return a;
 }

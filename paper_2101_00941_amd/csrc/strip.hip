@@ -74,7 +74,7 @@ __device__ __forceinline__ void strip_flush(i32x16 (&acc)[4], int q, int m, int 
 template <int TILE, int PASSES, bool EDGE>
 __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& b, int blk, int64_t t0, uint8_t* lds,
                                             int p, int lane, int K) {
-    constexpr int D = kStripStages;
+    constexpr int D = EDGE ? 2 : PASSES == 2 ? 4 : 3;   // steps of loads in registers, as many as fit
     const int64_t pitch = A.in_pitch;
     const uint32_t* const recs = reinterpret_cast<const uint32_t*>(A.offs) + static_cast<int64_t>(b.rec256) * 64;
     const int32_t* const rsv = A.base + static_cast<int64_t>(blk) * A.nchan_pad;
@@ -85,7 +85,7 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
 #pragma unroll
         for (int l = 0; l < 2; ++l) wdst[s][l] = strip_ring(TILE) + (p & 1) * kQuadBytes + entry_at(128 * s + 2 * lane + l);
 
-    // One buffer resource per step, based 16 bytes before its first row at the time tile; a
+    // One buffer resource per step, based kStripBias bytes before its first row at the time tile; a
     // row is reached through the scalar offset, which the range check counts: channels that
     // do not exist carry an offset beyond the range and read zeros (they enter the sums as
     // -128 per channel like every zero byte, and the final correction counts them). An EDGE
@@ -93,7 +93,7 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
     // would read outside moves to the nearest dword inside, and its bytes are shifted back to
     // their places when they are written to LDS (bytes from outside only reach outputs that
     // are not stored).
-    const uint8_t* sbase = EDGE ? A.in + 4 * p * pitch : A.in + t0 - 16;
+    const uint8_t* sbase = EDGE ? A.in + 4 * p * pitch : A.in + t0 - kStripBias;
     int nstep = 0;             // next step to load
     // per-step tables, 64 steps at a time, lane l holding step 64 n + l
     u32x4 off_tab{};           // offsets of the quad's rows from the step's base
@@ -108,7 +108,7 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
             off_tab = c < A.nchan_pad ? *reinterpret_cast<const u32x4*>(rsv + c) : u32x4{0u, 0u, 0u, 0u};
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-                if constexpr (!EDGE) off_tab[i] += 16u + static_cast<uint32_t>((4 * p + i) * pitch);
+                if constexpr (!EDGE) off_tab[i] += static_cast<uint32_t>(kStripBias + (4 * p + i) * pitch);
                 if (c + i >= A.nchan) off_tab[i] = kStripNoRow;
             }
             // wait for the tables here, so that the steps that do not load them need no wait
@@ -178,6 +178,7 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
             *reinterpret_cast<uint32_t*>(lds + strip_recs(TILE) + 256 * (2 * (n & 1) + p) + 4 * lane) = st_rec[s];
     };
 
+    // steps past the last one load rows that do not exist: zeros
 #pragma unroll
     for (int s = 0; s < D; ++s) issue(s);
     write(0, 0);
@@ -185,21 +186,26 @@ __device__ __forceinline__ void strip_stage(const DedispArgs& A, const DmBlock& 
     write(1, 1);
     issue(1);
     step_barrier();
+    auto step = [&](int s, int k) {
+        step_barrier();
+        write((s + 2) % D, k + 2);
+        issue((s + 2) % D);
+    };
     // (the loop's own waits are counted only if nothing is in flight where it is entered)
     __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0)
-    // whole rounds of D steps, so that the loop has one exit: the waits for a stage's loads
-    // are counted over the loads issued after it on every path, and an exit per step would
-    // join states in which fewer are
+    // whole rounds of D steps in a loop with one exit: the waits for a stage's loads are
+    // counted over the loads issued after it on every path, and an exit per step would join
+    // states in which fewer are. The remaining steps follow.
     int k = 0;
-    do {
+    for (; k + D <= K; k += D) {
 #pragma unroll
-        for (int s = 0; s < D; ++s) {
-            step_barrier();
-            write((s + 2) % D, k + 2);
-            issue((s + 2) % D);
-            ++k;
-        }
-    } while (k < K);
+        for (int s = 0; s < D; ++s) step(s, k + s);
+    }
+#pragma unroll
+    for (int s = 0; s < D - 1; ++s) {
+        if (k + s >= K) break;
+        step(s, k + s);
+    }
 }
 
 // The contracting waves: strip `wave` of every run that has it.
@@ -324,14 +330,15 @@ __device__ __forceinline__ void strip_contract(const DedispArgs& A, const DmBloc
 }
 
 template <int TILE>
-__device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64_t t0) {
+__device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64_t tile) {
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     const DmBlock b = load_block(A.blocks, blk);
+    const int64_t t0 = tile * TILE - b.lead;
+    if (t0 + b.lead - b.span >= A.n_out) return;   // past the end of every trial
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int groups = (A.nchan + 7) / 8;
-    // steps of two groups, in whole rounds of the load stages (the tables are padded)
-    const int K = ((groups + 1) / 2 + kStripStages - 1) / kStripStages * kStripStages;
+    const int K = (groups + 1) / 2;   // steps of two groups (the tables are padded)
     for (int i = tid; i < strip_ring(TILE) / 16; i += kThreads) reinterpret_cast<u32x4*>(lds)[i] = u32x4{0u, 0u, 0u, 0u};
     // the staging waves are the oldest of their SIMDs, which win issue
     if (wave >= kStage) {
@@ -353,37 +360,40 @@ __device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64
 
     const int32_t corr = 128 * 8 * groups;
     const int32_t* acc_lds = reinterpret_cast<const int32_t*>(lds + kAcc0);
+    // thread: trial tid % 32, 4 samples per item
+    const int d = tid & 31;
+    const int32_t* const skews = A.offs + static_cast<int64_t>(b.rec256) * 64 + static_cast<int64_t>(A.nchan_pad >> 3) * 64 +
+                                 ((A.nchan_pad >> 3) + 63) / 64 * 64;
+    const int64_t td = t0 + skews[d];
+    int32_t* const orow = A.out + static_cast<int64_t>(b.first + d) * A.out_pitch;
+    if (d >= b.count) return;
 #pragma unroll 1
-    for (int idx = tid; idx < TILE * 8; idx += kThreads) {   // 4 samples x 1 trial per item
-        const int d = idx & 31, tq = idx >> 5;
+    for (int tq = tid >> 5; tq < TILE / 4; tq += kThreads / 32) {
         int32_t v[4];
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) v[jj] = acc_lds[(4 * tq + jj) * 32 + d] + corr;
-        if (d < b.count) {
-            int32_t* orow = A.out + static_cast<int64_t>(b.first + d) * A.out_pitch;
-            const int64_t t = t0 + 4 * tq;
-            if (t + 4 <= A.n_out) {
-                *reinterpret_cast<u32x4*>(orow + t) = u32x4{static_cast<uint32_t>(v[0]), static_cast<uint32_t>(v[1]),
-                                                           static_cast<uint32_t>(v[2]), static_cast<uint32_t>(v[3])};
-            } else {
+        const int64_t t = td + 4 * tq;
+        if (t >= 0 && t + 4 <= A.n_out) {
+            *reinterpret_cast<u32x4*>(orow + t) = u32x4{static_cast<uint32_t>(v[0]), static_cast<uint32_t>(v[1]),
+                                                       static_cast<uint32_t>(v[2]), static_cast<uint32_t>(v[3])};
+        } else {
 #pragma unroll
-                for (int jj = 0; jj < 4; ++jj)
-                    if (t + jj < A.n_out) orow[t + jj] = v[jj];
-            }
+            for (int jj = 0; jj < 4; ++jj)
+                if (t + jj >= 0 && t + jj < A.n_out) orow[t + jj] = v[jj];
         }
     }
 }
 
 __global__ __launch_bounds__(kThreads, 4) void dedisp_strip_kernel(DedispArgs a) {
     const int bid = xcd_remap(blockIdx.x, gridDim.x);
-    dedisp_strip<kStripTile>(a, bid % a.nblk, static_cast<int64_t>(bid / a.nblk) * kStripTile);
+    dedisp_strip<kStripTile>(a, bid % a.nblk, bid / a.nblk);
 }
 
 __global__ __launch_bounds__(kThreads, 4) void dedisp_strip_batch_kernel(const DedispArgs* __restrict__ args,
                                                                          const int64_t* __restrict__ item_begin, int nbeams,
                                                                          int64_t total, unsigned long long* counter) {
     batch_items(args, item_begin, nbeams, total, counter, [](const DedispArgs& a, int blk, int64_t tile) {
-        dedisp_strip<kStripTile>(a, blk, tile * kStripTile);
+        dedisp_strip<kStripTile>(a, blk, tile);
     });
 }
 

@@ -432,12 +432,13 @@ namespace {
 
 struct StripRun {
     int s0, s1;                // substeps [s0, s1)
-    int32_t emin, emax;        // over the block's trials
+    int32_t emin, emax;        // of E' over the block's trials
 };
 
 // Residual ranges of one DM block, per substep (cps channels) and trial.
 struct StripBlock {
     int first, count, cps, nsub;
+    int32_t skew[32];
     std::vector<int32_t> lo, hi;   // [nsub][count] min and max over the substep of f(d, c)
 };
 
@@ -452,6 +453,7 @@ void strip_ranges(const aa_plan_s* p, int first, int count, int cps, StripBlock&
     const int32_t* ref = &p->shifts[static_cast<size_t>(first + count / 2) * nchan];
     for (int i = 0; i < count; ++i) {
         const int32_t* sd = &p->shifts[static_cast<size_t>(first + i) * nchan];
+        int32_t fmin = INT32_MAX, fmax = INT32_MIN;
         for (int s = 0; s < b.nsub; ++s) {
             const int c0 = s * cps, c1 = std::min(c0 + cps, nchan);
             int32_t l = INT32_MAX, h = INT32_MIN;
@@ -462,7 +464,14 @@ void strip_ranges(const aa_plan_s* p, int first, int count, int cps, StripBlock&
             }
             b.lo[static_cast<size_t>(s) * count + i] = l;
             b.hi[static_cast<size_t>(s) * count + i] = h;
+            if (c0 < nchan) {
+                fmin = std::min(fmin, l);
+                fmax = std::max(fmax, l);
+            }
         }
+        // the middle of the trial's range, to a multiple of 4 (floor)
+        const int32_t mid = fmin + (fmax - fmin) / 2;
+        b.skew[i] = -(mid - ((mid % 4) + 4) % 4);
     }
 }
 
@@ -492,7 +501,11 @@ bool strip_runs(const StripBlock& b, int spread_max, std::vector<StripRun>& runs
             }
             ++s1;
         }
-        const int32_t emin = *std::min_element(l, l + n), emax = *std::max_element(l, l + n);
+        int32_t emin = INT32_MAX, emax = INT32_MIN;
+        for (int i = 0; i < n; ++i) {
+            emin = std::min(emin, l[i] + b.skew[i]);
+            emax = std::max(emax, l[i] + b.skew[i]);
+        }
         if (emax - emin > spread_max) return false;
         runs.push_back(StripRun{s, s1, emin, emax});
         s = s1;
@@ -518,7 +531,7 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
     if (tile % 32 || tile < 128 || strip_spread(tile) < 0 || (shape != 0 && shape != 4 && shape != 8))
         return fail(AA_EINVAL, "strip tiling: bad tile or shape");
     const int nchan = p->nchan, npad = strip_nchan_pad(nchan), K = npad / 8, Kinfo = (K + 63) / 64 * 64;
-    const size_t blk_dwords = static_cast<size_t>(K) * 64 + Kinfo;
+    const size_t blk_dwords = static_cast<size_t>(K) * 64 + Kinfo + 64;
     blocks.clear();
     rs.clear();
     rec.clear();
@@ -568,7 +581,7 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
                 for (int c = s * cps; c < std::min(s * cps + cps, nchan); ++c) rs[rat + c] = ref[c] + r.emin;
                 for (int i = 0; i < count; ++i) {
                     const int32_t* sd = &p->shifts[static_cast<size_t>(d0 + i) * nchan];
-                    const uint32_t e = static_cast<uint32_t>(E[i] - r.emin);
+                    const uint32_t e = static_cast<uint32_t>(E[i] + b.skew[i] - r.emin);
                     for (int h = 0; h < 2; ++h) {
                         uint32_t v = 0;
                         if (cps == 8) {
@@ -592,9 +605,11 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
         }
         if (cps == 8)
             for (int k = 0; k < K; ++k) info[k] |= (info[k] & 1u) << 1;
+        std::memcpy(&rec[at + static_cast<size_t>(K) * 64 + Kinfo], b.skew, sizeof(int32_t) * count);
+        const int32_t lead = *std::max_element(b.skew, b.skew + count), low = *std::min_element(b.skew, b.skew + count);
         const int32_t* r0 = &rs[rat];
         DmBlock blk{d0, count, row_bytes, *std::min_element(r0, r0 + npad), *std::max_element(r0, r0 + npad), cps,
-                    static_cast<int32_t>(at / 64)};
+                    static_cast<int32_t>(at / 64), lead, lead - low};
         blocks.push_back(blk);
         d0 += count;
     }
@@ -611,6 +626,7 @@ int prepare_strip(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     t.bd = 32;
     t.nchan_pad = strip_nchan_pad(p->nchan);
     t.max_row = 0;
+    for (const DmBlock& b : blocks) t.span = std::max(t.span, b.span);
     t.blocks = blocks;
     if (p->device >= 0) {
                 int rc = upload(&t.d_blocks, blocks);

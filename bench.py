@@ -58,7 +58,7 @@ TRAFFIC_BYTES = {
     ("survey_4096ch_1M", 20): (196.62e9 + 12.15e9, "2a64072bc06edccd"),
     ("survey_4096ch_1M", 23): (466.86e9 + 12.15e9, "2a64072bc06edccd"),
 }
-KERNEL_SOURCES = ("dedisp.hip", "tiling.cpp", "aa_internal.h", "xcd.h")
+KERNEL_SOURCES = ("dedisp.hip", "strip.hip", "dedisp_device.h", "tiling.cpp", "aa_internal.h", "xcd.h")
 # the part of aa_internal.h that the dedispersion kernels use: tiling constants, variant
 # and table layouts, launch arguments
 INTERNAL_SPAN = ("// Dedispersion tiling.", "// Single-pulse-search tiling")
@@ -641,7 +641,7 @@ def main():
     vinfo = variants[plan.variant]
     entry = TRAFFIC_BYTES.get((w["name"], plan.variant)) if not a.ndm else None
     traffic = entry[0] if entry and entry[1] == kernel_digest() else None
-    if vinfo["layout"] in (4, 5, 6):
+    if vinfo["layout"] in (4, 5, 6, 8):
         # a contraction on the i8 matrix cores, priced against their dense peak; one op
         # per useful byte add (the one-hot weights are not counted)
         roofline = {"bound": "mfma", "dtype": "i8", "kernel": "dedisp_kernel (i8 matrix cores)",

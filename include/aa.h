@@ -134,7 +134,7 @@ int aa_dedisperse(aa_plan_t plan, const uint8_t* d_in, int64_t in_pitch, int64_t
  *   aa_variant_count()            number of variants
  *   aa_variant_info(v, out)       shape of variant v
  *   aa_plan_set_variant(plan, v)  prepare v and use it for aa_dedisperse (a new plan uses
- *                                 variant 12, the 16-wave i8 matrix-core kernel)
+ *                                 variant 12, the i8 matrix-core strip kernel)
  *   aa_plan_get_variant(plan, v)  variant in use
  *   aa_autotune(...)              time every variant on the caller's buffers (reps runs
  *                                 each, HIP events on `stream`), select the fastest,
@@ -155,9 +155,11 @@ typedef struct {
     int32_t layout;   /* 0, 3: a lane owns 16 contiguous samples; 1, 2: four groups of 4, 256 apart
                          (2 reuses a window when the next trial has the same offset);
                          4, 5: i8 matrix-core contraction over an exact split of the shift table
-                         (4 or 8 channels per step); 6: both, chosen per block of trials */
+                         (4 or 8 channels per step); 6: both, chosen per block of trials;
+                         8: the same contraction on 128-row strips, with separate staging waves */
     int32_t time_tile;   /* output samples per work-group */
-    int32_t depth;       /* staging buffers per work-group (loads run depth - 1 passes ahead) */
+    int32_t depth;       /* staging buffers per work-group (loads run depth - 1 passes ahead;
+                            layout 8 keeps further loads in registers) */
     int32_t max_tiles;   /* layouts 4-6: a channel block spans at most 32 * max_tiles rows of the
                             shifted time axis (31 or 63); 0 for the other layouts */
 } aa_variant_t;

@@ -169,7 +169,7 @@ extern const DedispVariant kDedispVariants[kNumDedispVariants];
 inline bool variant_takes_pitch(int variant, int64_t in_pitch) {
     return kDedispVariants[variant].layout != 7 || in_pitch <= kQuadMaxPitch;
 }
-constexpr int kDefaultDedispVariant = 12;   // i8 matrix cores, 16 waves
+constexpr int kDefaultDedispVariant = 12;   // i8 matrix cores, strip kernel
 
 // Single-pulse-search tiling: a work-group covers kSpsRows DM rows and kSpsTile starts.
 constexpr int kSpsTile = 256;

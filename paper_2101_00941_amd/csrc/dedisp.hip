@@ -1002,12 +1002,14 @@ __global__ void reset_counter_kernel(unsigned long long* c) { *c = 0ull; }
 // Indexed by DedispVariant::id (tiling.cpp); layout 4-6 entries repeat the variant's
 // time tile, depth and channel-block span; layout 7 entries are <samples per lane, waves,
 // 7, tile, chunks per wave, 0, waves per SIMD>.
+// (12, the strip kernel, is in strip.hip; its place repeats variant 25)
 #define AA_VARIANTS(K)                                                                           \
     K<4, 4, 1>, K<2, 8, 1>, K<4, 8, 1>, K<2, 16, 1>, K<2, 8, 0>, K<4, 4, 0>, K<2, 8, 3>, K<4, 4, 3>, \
         K<2, 8, 2>, K<4, 8, 2>, K<4, 4, 2>, K<4, 8, 4, 1024, 3>, K<2, 16, 4, 1024, 3>, K<2, 16, 4, 768, 7>, \
         K<4, 8, 4, 512, 3, 31, 4>, K<2, 16, 4, 512, 3, 31, 8>, K<4, 8, 4, 480, 4, 31, 4>, K<2, 16, 5, 864, 3, 63>, \
         K<2, 16, 4, 960, 4, 63>, K<2, 16, 4, 896, 5, 63>, K<2, 16, 6, 864, 3, 63>, K<2, 4, 7, 512, 4, 0, 4>, \
-        K<2, 8, 7, 1024, 4, 0, 4>, K<1, 16, 7, 1024, 2, 0, 8>, K<1, 8, 7, 512, 2, 0, 8>
+        K<2, 8, 7, 1024, 4, 0, 4>, K<1, 16, 7, 1024, 2, 0, 8>, K<1, 8, 7, 512, 2, 0, 8>, \
+        K<2, 16, 4, 1024, 3>
 const DedispFn kKernels[] = {AA_VARIANTS(dedisp_kernel)};
 const DedispBatchFn kBatchKernels[] = {AA_VARIANTS(dedisp_batch_kernel)};
 DedispFn kernel_of(int variant) { return kDedispVariants[variant].layout == 8 ? kStripKernel : kKernels[variant]; }

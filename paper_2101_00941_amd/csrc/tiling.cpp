@@ -25,7 +25,8 @@ const DedispVariant kDedispVariants[kNumDedispVariants] = {
     // 32 trials per block, i8 matrix cores; waves, time tile, staging depth and the
     // channel-block span vary. The kernel table in dedisp.hip repeats these parameters.
     {11, 8, 4, mfma_lds_bytes(1024, 3, 63), 4, 1024, 3, 63},   // 512 threads, 8 tiles per wave
-    {12, 16, 2, mfma_lds_bytes(1024, 3, 63), 4, 1024, 3, 63},  // 1024 threads, 4 tiles per wave
+    // the plan default: matrix cores over 128-row strips (12 contracting and 4 staging waves)
+    {12, 16, 2, strip_lds_bytes(kStripTile), 8, kStripTile, 2, 0},  // 1024 threads
     {13, 16, 2, mfma_lds_bytes(768, 7, 63), 4, 768, 7, 63},    // 1024 threads, 4 tiles per wave
     // two work-groups per CU (LDS <= 80 KB, registers for 4 or 8 waves per SIMD)
     {14, 8, 4, mfma_lds_bytes(512, 3, 31), 4, 512, 3, 31},     // 512 threads, 4 tiles per wave
@@ -44,8 +45,7 @@ const DedispVariant kDedispVariants[kNumDedispVariants] = {
     {22, 8, 4, quad_lds_bytes(32), 7, 1024, 32, 0},   // 512 threads, 2 samples per lane
     {23, 16, 2, quad_lds_bytes(32), 7, 1024, 32, 0},  // 1024 threads, 1 sample per lane
     {24, 8, 4, quad_lds_bytes(16), 7, 512, 16, 0},    // 512 threads, 1 sample per lane
-    // matrix cores over 128-row strips, 32 trials per block, separate staging waves
-    {25, 16, 2, strip_lds_bytes(kStripTile), 8, kStripTile, 2, 0},   // 1024 threads
+    {25, 16, 2, mfma_lds_bytes(1024, 3, 63), 4, 1024, 3, 63},  // 1024 threads, 4 tiles per wave
 };
 
 void free_tables(DedispTables& t) {

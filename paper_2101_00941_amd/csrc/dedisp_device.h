@@ -14,21 +14,24 @@ extern const DedispBatchFn kStripBatchKernel;
 
 namespace {
 
-// A DM block's table entry, read through the constant address space: it is the same in
-// every lane and read-only for the launch, so its loads are scalar even where the table
-// pointer comes from memory (the persistent batch kernel reads it from the beam's
-// argument block).
-__device__ __forceinline__ DmBlock load_block(const DmBlock* blocks, int blk) {
-    static_assert(sizeof(DmBlock) % 4 == 0, "a DM block entry is whole dwords");
+// Read-only device data that is the same in every lane, read through the constant address
+// space so that its loads are scalar even where the pointer comes from memory (the persistent
+// batch kernel reads it from the beam's argument block).
+template <class T>
+__device__ __forceinline__ T load_uniform(const T* src) {
+    static_assert(sizeof(T) % 4 == 0, "whole dwords");
     typedef const __attribute__((address_space(4))) int32_t* word_ptr;
-    const word_ptr p = (word_ptr)(const void*)(blocks + blk);
-    int32_t w[sizeof(DmBlock) / 4];
+    const word_ptr p = (word_ptr)(const void*)src;
+    int32_t w[sizeof(T) / 4];
 #pragma unroll
-    for (int i = 0; i < static_cast<int>(sizeof(DmBlock) / 4); ++i) w[i] = p[i];
-    DmBlock b;
-    __builtin_memcpy(&b, w, sizeof(b));
-    return b;
+    for (int i = 0; i < static_cast<int>(sizeof(T) / 4); ++i) w[i] = p[i];
+    T v;
+    __builtin_memcpy(&v, w, sizeof(v));
+    return v;
 }
+
+// A DM block's table entry: read-only for the launch.
+__device__ __forceinline__ DmBlock load_block(const DmBlock* blocks, int blk) { return load_uniform(blocks + blk); }
 
 constexpr int kRawBufferFlags = 0x00020000;   // word 3 of a gfx9 buffer resource: raw 32-bit data
 
@@ -59,13 +62,13 @@ __device__ __forceinline__ void batch_items(const DedispArgs* __restrict__ args,
         int lo = 0, hi = nbeams - 1;
         while (lo < hi) {
             const int mid = (lo + hi + 1) >> 1;
-            if (item_begin[mid] <= it) lo = mid; else hi = mid - 1;
+            if (load_uniform(item_begin + mid) <= it) lo = mid; else hi = mid - 1;
         }
         // the beam is the same in every lane; stating it keeps the beam's arguments and
         // the tile's step records in scalar registers
         lo = __builtin_amdgcn_readfirstlane(lo);
-        const DedispArgs a = args[lo];
-        const int64_t local = it - item_begin[lo];
+        const DedispArgs a = load_uniform(args + lo);
+        const int64_t local = it - load_uniform(item_begin + lo);
         tile(a, static_cast<int>(local % a.nblk), local / a.nblk);
         __syncthreads();   // the next item restages the LDS
     }

@@ -335,7 +335,11 @@ __device__ __forceinline__ void dedisp_strip(const DedispArgs& A, int blk, int64
     const DmBlock b = load_block(A.blocks, blk);
     const int64_t t0 = tile * TILE - b.lead;
     if (t0 + b.lead - b.span >= A.n_out) return;   // past the end of every trial
-    const int tid = threadIdx.x, lane = tid & 63;
+    // (opaque, so that the batch kernel's item loop does not keep per-lane values of every
+    // role in registers across items)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int groups = (A.nchan + 7) / 8;
     const int K = (groups + 1) / 2;   // steps of two groups (the tables are padded)

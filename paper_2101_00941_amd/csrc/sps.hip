@@ -4,11 +4,13 @@
 //               float64, then the per-width normalisation wmu_w = w*mu and
 //               r_w = 1/(sigma*sqrt(w)), and each width's smallest window sum whose
 //               S/N reaches the threshold.
-//   sps_detect  per (8 DM rows, 256 starts) tile: LDS prefix sums give the boxcars,
-//               an integer screen against those sums drops the cells whose best S/N
-//               is below the threshold, and the rest get the float64 best S/N and a
-//               3x3 peak test on a one-sample, one-row halo. The result is a bit mask
-//               of candidates per row, plus integer per-row counts.
+//   sps_screen  per wave two DM rows and a run of tiles of 256 starts: LDS prefix sums
+//               give the boxcars, an integer screen against those sums drops the cells
+//               whose best S/N is below the threshold, and the rest get the float64 best
+//               S/N and a 3x3 peak test on a one-sample, one-row halo. The result is a bit
+//               mask of candidates per row, plus integer per-row counts.
+//   sps_best    instead of it where the best plane is an output: the float64 best S/N of
+//               every cell of an (8 DM rows, 256 starts) tile, then the peak test.
 //   sps_emit    one work-group per DM row. The row's output offset is the sum of
 //               the counts of the rows before it. A block scan of the mask ranks each
 //               candidate, and the candidate is written in (dm, t) order. Its S/N and
@@ -19,10 +21,13 @@
 // streamed search stalled on atomics combined with event waits.
 #pragma clang fp contract(off)
 
+#include <algorithm>
 #include <mutex>
 #include <string>
+#include <type_traits>
 
 #include "aa_internal.h"
+#include "dedisp_device.h"
 #include "numerics.h"
 #include "screen.h"
 #include "xcd.h"
@@ -43,7 +48,6 @@ struct SpsConst {
     int32_t smask[kMaxWidths];
 };
 
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
 
 // Inclusive prefix sum over the 64 lanes of a wave (modulo 2^32): shifts by 1, 2, 4 and
 // 8 lanes inside each row of 16, then the last lane of row 0 (and of row 2) is added to
@@ -85,9 +89,9 @@ __device__ __forceinline__ void block_moments(const int32_t* row, int64_t lo, in
         }
     };
     if (threadIdx.x < head) add(p[threadIdx.x]);
-    const u32x4_t* q = reinterpret_cast<const u32x4_t*>(p + head);
+    const u32x4* q = reinterpret_cast<const u32x4*>(p + head);
     for (int64_t i = threadIdx.x; i < n4; i += 256) {
-        const u32x4_t v = q[i];
+        const u32x4 v = q[i];
         add(v[0]);
         add(v[1]);
         add(v[2]);
@@ -164,58 +168,151 @@ __global__ __launch_bounds__(256) void sps_stats_kernel(const int32_t* __restric
 constexpr int kHaloRows = kSpsRows + 2;
 constexpr int kHaloCols = kSpsTile + 2;
 
-// LDS of a detection work-group, in this order: 8 bytes, prefix sums [kHaloRows][ps]
-// (u32, row stride ps >= kSpsTile + 2 + wmax, a multiple of 4, so that entry 2 of every
-// row is 16-byte aligned), then (EXACT only) the float64 best S/N of every halo cell
-// [kHaloRows][kHaloCols]. The float64 normalisation is read from global memory (cached)
-// by the exact evaluations, which only cells passing the screen need.
-struct DetectLds {
-    int tail, total;   // byte offsets
-};
-__host__ __device__ inline int detect_row_stride(int wmax) { return 4 * ((kSpsTile + wmax + 3) / 4 + 1); }
-__host__ __device__ inline DetectLds detect_lds(int wmax, int nw, bool exact) {
-    DetectLds L;
-    (void)nw;
-    L.tail = (8 + kHaloRows * detect_row_stride(wmax) * 4 + 15) / 16 * 16;
-    L.total = L.tail + (exact ? kHaloRows * kHaloCols * 8 : 0);
-    return L;
+// 4-column groups of a tile's prefix sums (the starts and the widest boxcar past the last of
+// them), and the row stride of a tile's prefix sums with the halo column: entry 1 of a row,
+// the prefix at the tile's first start, is 16-byte aligned if the rows begin 12 bytes into
+// an aligned buffer.
+__host__ __device__ inline int prefix_groups(int wmax) { return (kSpsTile + wmax + 3) / 4; }
+__host__ __device__ inline int prefix_row_stride(int wmax) { return 4 * (prefix_groups(wmax) + 1); }
+constexpr int kPrefixHead = 12;
+__host__ __device__ inline int prefix_bytes(int wmax, int rows) {
+    return (kPrefixHead + rows * prefix_row_stride(wmax) * 4 + 15) / 16 * 16;
+}
+// LDS of a work-group of the exact detection: prefix sums of kHaloRows rows, then the
+// float64 best S/N of every halo cell [kHaloRows][kHaloCols].
+__host__ __device__ inline int best_lds(int wmax) { return prefix_bytes(wmax, kHaloRows) + kHaloRows * kHaloCols * 8; }
+
+// n columns of row d of the plane from column c on as a buffer: each dword past them, or of
+// a trial outside 0 .. ndm - 1, reads as 0. The arguments are the same in every lane.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(const int32_t* dd, int64_t dd_pitch, int ndm, int d, int64_t c,
+                                                             int n) {
+    const bool in = d >= 0 && d < ndm && n > 0;
+    const int32_t* src = dd + (in ? d * dd_pitch + c : 0);
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(src), 0, __builtin_amdgcn_readfirstlane(in ? 4 * n : 0),
+                                             kRawBufferFlags);
+}
+// columns from col on of a plane of dd_n columns, at most limit
+__device__ __forceinline__ int columns_left(int64_t dd_n, int64_t col, int limit) {
+    return dd_n - col >= limit ? limit : static_cast<int>(dd_n - col);
+}
+__device__ __forceinline__ u32x4 load_group(__amdgpu_buffer_rsrc_t rsrc, int u) {
+    return __builtin_amdgcn_raw_buffer_load_b128(rsrc, 16 * u, 0, 0);
+}
+// Exclusive prefix sums of a wave's 256 columns (lane l: columns 4 l .. 4 l + 3) on top of
+// carry, which moves on to the sum past them.
+__device__ __forceinline__ u32x4 scan_group(const u32x4& x, uint32_t& carry) {
+    const uint32_t a = x[0], b = a + x[1], c = b + x[2], e = c + x[3];
+    const uint32_t incl = wave_incl_scan(e);
+    const uint32_t base = carry + (incl - e);
+    carry += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
+    return u32x4{base, base + a, base + b, base + c};
 }
 
-// Exact value of one halo cell: best S/N over the widths, float64, same operation order
-// as the oracle. -inf outside the range of rows and starts.
-__device__ __forceinline__ double exact_best(const uint32_t* pre, int stride, const double* nj, int d0,
-                                             const SpsConst& sc, int r, int c, bool valid, uint32_t t) {
-    if (!valid) return -__builtin_huge_val();
-    const uint32_t* pr = pre + r * stride + c;
-    const double* nr = nj + static_cast<int64_t>(d0 - 1 + r) * (2 * sc.nw);   // halo row r is trial d0 - 1 + r
-    double v = 0.0;
-    for (int k = 0; k < sc.nw; ++k) {
-        if (k >= sc.kfull && (t & static_cast<uint32_t>(sc.smask[k]))) continue;   // not on this width's grid
-        const uint32_t s = pr[sc.widths[k]] - pr[0];
-        const double snr = (static_cast<double>(s) - nr[k]) * nr[sc.nw + k];
-        if (k == 0 || snr > v) v = snr;
+// Prefix sums of N rows of a tile by one wave: trial dt[i] into the row at prow[i], entry j =
+// sum of D[t_tile0 - 1 + i] for i < j (modulo 2^32: every window sum is exact below 2^32).
+// col is the plane column of the tile's first start. The loads of all rows' first two groups
+// (all there are up to a width of 256) are issued before any scan, so that their latencies
+// overlap.
+template <int N>
+__device__ __forceinline__ void tile_prefix(const int32_t* dd, int64_t dd_pitch, int64_t dd_n, int ndm, int64_t col, int nq,
+                                            const int (&dt)[N], uint32_t* const (&prow)[N], int lane) {
+    u32x4 xs[N][2];
+    uint32_t first[N];   // D[t_tile0 - 1], the halo column (0 before the plane's first column)
+    const int n = columns_left(dd_n, col, 4 * nq);
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const __amdgpu_buffer_rsrc_t rsrc = row_buffer(dd, dd_pitch, ndm, dt[i], col, n);
+        const __amdgpu_buffer_rsrc_t halo = row_buffer(dd, dd_pitch, ndm, dt[i], col - 1, col > 0 ? 1 : 0);
+        first[i] = __builtin_amdgcn_raw_buffer_load_b32(halo, 0, 0, 0);
+        xs[i][0] = load_group(rsrc, lane);
+        xs[i][1] = load_group(rsrc, 64 + lane);
     }
-    return v;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        uint32_t carry = static_cast<uint32_t>(__builtin_amdgcn_readfirstlane(static_cast<int>(first[i])));
+        auto scan = [&](const u32x4& x, int u) {
+            const u32x4 q = scan_group(x, carry);
+            if (u < nq) *reinterpret_cast<u32x4*>(prow[i] + 1 + 4 * u) = q;
+        };
+        scan(xs[i][0], lane);
+        scan(xs[i][1], 64 + lane);
+#pragma unroll 1
+        for (int u0 = 128; u0 < nq; u0 += 64)
+            scan(load_group(row_buffer(dd, dd_pitch, ndm, dt[i], col, n), u0 + lane), u0 + lane);
+        if (lane == 0) {
+            prow[i][0] = 0u;
+            prow[i][1 + 4 * nq] = carry;
+        }
+    }
 }
 
-// EXACT: every halo cell in float64 (needed when the best plane is an output).
-// Otherwise an integer screen runs first (min_passing_sum): cells whose best S/N cannot
-// reach the threshold are dropped, and only the others, with their 8 neighbours, are
-// evaluated in float64 for the 3x3 peak decision. The launcher takes this path only when
-// every window sum is below 2^31.
-template <bool EXACT>
-__global__ __launch_bounds__(256) void sps_detect_kernel(
+// One row's normalisation across the lanes of a wave: lane k holds w*mu and 1/(sigma*sqrt(w))
+// of width k.
+struct RowNorm {
+    double wmu, r;
+};
+__device__ __forceinline__ RowNorm load_norm(const double* nj, int d, bool valid, int nw, int lane) {
+    RowNorm n{0.0, 0.0};
+    if (valid && lane < nw) {
+        const double* p = nj + static_cast<int64_t>(d) * (2 * nw);
+        n.wmu = p[lane];
+        n.r = p[nw + lane];
+    }
+    return n;
+}
+__device__ __forceinline__ double lane_value(double v, int k) {
+    union { double d; int i[2]; } u;
+    u.d = v;
+    u.i[0] = __builtin_amdgcn_readlane(u.i[0], k);
+    u.i[1] = __builtin_amdgcn_readlane(u.i[1], k);
+    return u.d;
+}
+
+// Best S/N over the widths of N cells of each of R rows, float64, in the oracle's order of
+// operations: cell (i, c) has its prefix at pr[i][c], sits at start t[c], and row i has the
+// normalisation norm[i]. All cells advance together through the widths, so that their LDS
+// reads and float64 operations overlap.
+template <int R, int N>
+__device__ __forceinline__ void exact_best(const uint32_t* const (&pr)[R][N], const uint32_t (&t)[N],
+                                           const RowNorm (&norm)[R], const SpsConst& sc, int wlane, double (&v)[R][N]) {
+    uint32_t base[R][N];
+#pragma unroll
+    for (int i = 0; i < R; ++i)
+#pragma unroll
+        for (int c = 0; c < N; ++c) base[i][c] = pr[i][c][0];
+    for (int k = 0; k < sc.nw; ++k) {
+        const int w = __builtin_amdgcn_readlane(wlane, k);
+        const uint32_t sm = k >= sc.kfull ? static_cast<uint32_t>(sc.smask[k]) : 0u;   // not on this width's grid
+#pragma unroll
+        for (int i = 0; i < R; ++i) {
+            const double wmu = lane_value(norm[i].wmu, k), r = lane_value(norm[i].r, k);
+#pragma unroll
+            for (int c = 0; c < N; ++c) {
+                const uint32_t s = pr[i][c][w] - base[i][c];
+                const double snr = (static_cast<double>(s) - wmu) * r;
+                if (k == 0 || ((t[c] & sm) == 0 && snr > v[i][c])) v[i][c] = snr;
+            }
+        }
+    }
+}
+
+// The exact detection, for searches whose best plane is an output (and for window sums of
+// 2^31 and more): float64 best S/N of every cell of a tile of 8 rows and 256 starts with a
+// halo of one row and one start on each side, then the 3x3 peak test. Bound by the float64
+// operations (three per cell and width): 333 trials of a 77,777-sample band 0.14 ms; with the
+// row's normalisation read from the LDS for every cell and width it took 0.26 ms.
+__global__ __launch_bounds__(256) void sps_best_kernel(
     const int32_t* __restrict__ dd, int64_t dd_pitch, int64_t dd_t0, int64_t dd_n, int64_t t_begin,
     int64_t t_end, int64_t t_total, int32_t B, int32_t ndm, double threshold, SpsConst sc,
-    const double* __restrict__ norms, const uint32_t* __restrict__ smin_g, int32_t* __restrict__ rowcount,
+    const double* __restrict__ norms, int32_t* __restrict__ rowcount,
     uint32_t* __restrict__ mask, int64_t nwords, float* __restrict__ best_out, int64_t best_pitch) {
     extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
     const int nw = sc.nw;
-    const int tw = kSpsTile + 1 + sc.wmax;            // D columns t_tile0-1 .. t_tile0+255+wmax
-    const int pw = tw + 1;                            // prefix entries per row
-    const int ps = detect_row_stride(sc.wmax);        // row stride of the prefix sums
-    const DetectLds L = detect_lds(sc.wmax, nw, EXACT);
-    uint32_t* pre = reinterpret_cast<uint32_t*>(smem + 8);               // [kHaloRows][ps]
+    const int nq = prefix_groups(sc.wmax);
+    const int ps = prefix_row_stride(sc.wmax);
+    uint32_t* pre = reinterpret_cast<uint32_t*>(smem + kPrefixHead);                              // [kHaloRows][ps]
+    double* best = reinterpret_cast<double*>(smem + prefix_bytes(sc.wmax, kHaloRows));            // [kHaloRows][kHaloCols]
+    __shared__ int32_t cnt[kSpsRows];
 
     // XCD-aware order: each XCD walks consecutive time tiles of a row block, which share
     // their halo columns in its L2
@@ -225,234 +322,470 @@ __global__ __launch_bounds__(256) void sps_detect_kernel(
     const int64_t tt0 = t_begin + static_cast<int64_t>(bx) * kSpsTile;
     const int64_t tile_end = min(tt0 + kSpsTile, t_end);
     const int d0 = by * kSpsRows;
-    const int j = static_cast<int>((static_cast<uint64_t>(bx) * kSpsTile) / static_cast<uint32_t>(B));
+    const int j = bx / (B / kSpsTile);                // B is a multiple of kSpsTile
     const int64_t lo = max(tt0 - 1, static_cast<int64_t>(0));
     const int64_t hi = (t_total < 0 || tile_end < t_total) ? tile_end + 1 : tile_end;  // best valid in [lo, hi)
     const int tid = threadIdx.x;
-    const int wave = tid >> 6, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const double* nj = norms + static_cast<int64_t>(j) * ndm * (2 * nw);
+    const int wlane = lane < nw ? sc.widths[lane < kMaxWidths ? lane : 0] : 0;   // width of lane k
 
-    // halo row r (trial d0 - 1 + r) belongs to wave r % 4: the prefix sums of its D
-    // columns, pre[r][j] = sum of D[t_tile0 - 1 + i] for i < j
-    // (modulo 2^32: every window sum is exact below 2^32), for j < pw
+    // halo row r (trial d0 - 1 + r) belongs to wave r % 4
     {
-        const int64_t col0 = tt0 - 1 - dd_t0;          // plane column of i = 0
-        const int nq = (kSpsTile + sc.wmax + 3) / 4;   // 4-column groups from t_tile0 on
-        // a tile inside an aligned plane loads 16 bytes per lane and scans in registers
-        const bool fast = col0 >= 0 && col0 + 1 + 4 * nq <= dd_n && ((col0 + 1) & 3) == 0 && (dd_pitch & 3) == 0 &&
-                          (reinterpret_cast<uintptr_t>(dd) & 15) == 0;
-        const int ilo = col0 < 0 ? static_cast<int>(-col0) : 0;
-        const int ihi = static_cast<int>(min<int64_t>(tw, dd_n - col0));
-        // up to 128 groups (wmax <= 256): all of the wave's loads are issued before any
-        // scan, so their latencies overlap
-        const bool fast2 = fast && nq <= 128;
-        u32x4_t xs[3][2];
-        uint32_t firsts[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            firsts[i] = 0u;
-            xs[i][0] = xs[i][1] = u32x4_t{0u, 0u, 0u, 0u};
-            const int r = wave + 4 * i, d = d0 - 1 + r;
-            if (fast2 && r < kHaloRows && d >= 0 && d < ndm) {
-                const int32_t* src = dd + static_cast<int64_t>(d) * dd_pitch + col0;
-                firsts[i] = static_cast<uint32_t>(src[0]);
-#pragma unroll
-                for (int c = 0; c < 2; ++c)
-                    if (64 * c + lane < nq) xs[i][c] = *reinterpret_cast<const u32x4_t*>(src + 1 + 4 * (64 * c + lane));
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int r = wave + 4 * i;
-            if (r >= kHaloRows) break;
-            const int d = d0 - 1 + r;
-            const bool in = d >= 0 && d < ndm;
-            uint32_t* prow = pre + r * ps;
-            if (!in) {
-                for (int k = lane; k < ps; k += 64) prow[k] = 0u;
-                continue;
-            }
-            const int32_t* src = dd + static_cast<int64_t>(d) * dd_pitch + col0;
-            if (fast2) {
-                uint32_t carry = firsts[i];
-#pragma unroll
-                for (int c = 0; c < 2; ++c) {
-                    const int u = 64 * c + lane;
-                    const u32x4_t x = xs[i][c];
-                    const uint32_t a = x[0], b = a + x[1], cc = b + x[2], e = cc + x[3];
-                    const uint32_t incl = wave_incl_scan(e);
-                    const uint32_t base = carry + (incl - e);
-                    if (u < nq) *reinterpret_cast<u32x4_t*>(prow + 2 + 4 * u) = u32x4_t{base + a, base + b, base + cc, base + e};
-                    carry += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
-                }
-                if (lane == 0) {
-                    prow[0] = 0u;
-                    prow[1] = firsts[i];
-                }
-            } else if (fast) {
-                // lane holds columns t_tile0 + 4u .. + 3, u = lane, lane + 64, ...
-                const uint32_t first = static_cast<uint32_t>(src[0]);
-                uint32_t carry = first;
-                for (int u0 = 0; u0 < nq; u0 += 64) {
-                    const int u = u0 + lane;
-                    u32x4_t x = {0u, 0u, 0u, 0u};
-                    if (u < nq) x = *reinterpret_cast<const u32x4_t*>(src + 1 + 4 * u);
-                    const uint32_t a = x[0], b = a + x[1], c = b + x[2], e = c + x[3];
-                    const uint32_t incl = wave_incl_scan(e);
-                    const uint32_t base = carry + (incl - e);
-                    if (u < nq) *reinterpret_cast<u32x4_t*>(prow + 2 + 4 * u) = u32x4_t{base + a, base + b, base + c, base + e};
-                    carry += static_cast<uint32_t>(__builtin_amdgcn_readlane(static_cast<int>(incl), 63));
-                }
-                if (lane == 0) {
-                    prow[0] = 0u;
-                    prow[1] = first;
-                }
-            } else {
-                // columns outside the plane count as 0; then the prefix in place, by the
-                // same wave (LDS operations of one wave complete in order)
-                if (lane == 0) prow[0] = 0u;
-                for (int i = lane; i < tw; i += 64) prow[1 + i] = (i >= ilo && i < ihi) ? static_cast<uint32_t>(src[i]) : 0u;
-                const int per = (pw + 63) / 64;
-                const int a = lane * per, b = min(a + per, pw);
-                uint32_t s = 0;
-                for (int i = a; i < b; ++i) s += prow[i];
-                uint32_t run = wave_incl_scan(s) - s;
-                for (int i = a; i < b; ++i) {
-                    run += prow[i];
-                    prow[i] = run;
-                }
-            }
+        const int rows[2] = {wave, wave + 4};
+        const int dt[2] = {d0 - 1 + rows[0], d0 - 1 + rows[1]};
+        uint32_t* const prow[2] = {pre + rows[0] * ps, pre + rows[1] * ps};
+        tile_prefix<2>(dd, dd_pitch, dd_n, ndm, tt0 - dd_t0, nq, dt, prow, lane);
+        if (wave + 8 < kHaloRows) {
+            const int dl[1] = {d0 - 1 + wave + 8};
+            uint32_t* const pl[1] = {pre + (wave + 8) * ps};
+            tile_prefix<1>(dd, dd_pitch, dd_n, ndm, tt0 - dd_t0, nq, dl, pl, lane);
         }
     }
-    // screen thresholds of the inner rows wave + 1 and wave + 5 (from the statistics
-    // kernel): lane k holds width k's smallest passing window sum (kNever if none)
-    uint32_t smin[2] = {kNever, kNever};
-    const int wlane = lane < nw ? sc.widths[lane < kMaxWidths ? lane : 0] : 0;   // width of lane k
-    if constexpr (!EXACT) {
+    if (tid < kSpsRows) cnt[tid] = 0;
+    __syncthreads();
+    // halo row r by wave r % 4, a lane's columns lane + 64 q
+    constexpr int NC = (kHaloCols + 63) / 64;
+    for (int r = wave; r < kHaloRows; r += 4) {
+        const int d = d0 - 1 + r;
+        const bool in = d >= 0 && d < ndm;
+        const RowNorm norm[1] = {load_norm(nj, d, in, nw, lane)};
+        const uint32_t* pr[1][NC];
+        uint32_t t[NC];
+        double v[1][NC];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int d = d0 + wave + 4 * h;
-            if (lane < nw && d < ndm) smin[h] = smin_g[(static_cast<int64_t>(j) * ndm + d) * nw + lane];
+        for (int q = 0; q < NC; ++q) {
+            const int c = min(64 * q + lane, kHaloCols - 1);
+            pr[0][q] = pre + r * ps + c;
+            t[q] = static_cast<uint32_t>(tt0 - 1 + c);
+            v[0][q] = 0.0;
+        }
+        exact_best<1, NC>(pr, t, norm, sc, wlane, v);
+#pragma unroll
+        for (int q = 0; q < NC; ++q) {
+            const int c = 64 * q + lane;
+            const int64_t tc = tt0 - 1 + c;
+            if (c < kHaloCols) best[r * kHaloCols + c] = in && tc >= lo && tc < hi ? v[0][q] : -__builtin_huge_val();
         }
     }
     __syncthreads();
-    if constexpr (EXACT) {
-        double* best = reinterpret_cast<double*>(smem + L.tail);         // [kHaloRows][kHaloCols]
-        __shared__ int32_t cnt[kSpsRows];
-        if (tid < kSpsRows) cnt[tid] = 0;
-        for (int i = tid; i < kHaloRows * kHaloCols; i += 256) {
-            const int r = i / kHaloCols, c = i - r * kHaloCols;
-            const int d = d0 - 1 + r;
-            const int64_t t = tt0 - 1 + c;
-            best[i] = exact_best(pre, ps, nj, d0, sc, r, c, d >= 0 && d < ndm && t >= lo && t < hi,
-                                 static_cast<uint32_t>(t));
+    // 3x3 peak test for the inner rows, 64 consecutive starts per wave step
+    for (int item = tid; item < kSpsRows * kSpsTile; item += 256) {
+        const int ri = item / kSpsTile, tc = item - ri * kSpsTile;
+        const int d = d0 + ri;
+        const int64_t t = tt0 + tc;
+        bool ok = false;
+        if (d < ndm && t < tile_end) {
+            const double* m = best + (ri + 1) * kHaloCols + (tc + 1);
+            const double v = m[0];
+            ok = v >= threshold && v > m[-kHaloCols - 1] && v > m[-kHaloCols] && v > m[-kHaloCols + 1] &&
+                 v > m[-1] && v >= m[1] && v >= m[kHaloCols - 1] && v >= m[kHaloCols] && v >= m[kHaloCols + 1];
+            if (best_out) best_out[static_cast<int64_t>(d) * best_pitch + (t - t_begin)] = static_cast<float>(v);
         }
-        __syncthreads();
-        // 3x3 peak test for the inner rows, 64 consecutive starts per wave step
-        for (int item = tid; item < kSpsRows * kSpsTile; item += 256) {
-            const int ri = item / kSpsTile, tc = item - ri * kSpsTile;
-            const int d = d0 + ri;
-            const int64_t t = tt0 + tc;
-            bool ok = false;
-            if (d < ndm && t < tile_end) {
-                const double* m = best + (ri + 1) * kHaloCols + (tc + 1);
-                const double v = m[0];
-                ok = v >= threshold && v > m[-kHaloCols - 1] && v > m[-kHaloCols] && v > m[-kHaloCols + 1] &&
-                     v > m[-1] && v >= m[1] && v >= m[kHaloCols - 1] && v >= m[kHaloCols] && v >= m[kHaloCols + 1];
-                if (best_out) best_out[static_cast<int64_t>(d) * best_pitch + (t - t_begin)] = static_cast<float>(v);
-            }
-            const uint64_t bal = __ballot(ok);
-            if (lane == 0 && d < ndm) {
-                const int64_t w = (tt0 - t_begin) / 32 + tc / 32;
-                *reinterpret_cast<uint64_t*>(mask + static_cast<int64_t>(d) * nwords + w) = bal;
-                if (bal) atomicAdd(&cnt[ri], __popcll(bal));
+        const uint64_t bal = __ballot(ok);
+        if (lane == 0 && d < ndm) {
+            const int64_t w = (tt0 - t_begin) / 32 + tc / 32;
+            *reinterpret_cast<uint64_t*>(mask + static_cast<int64_t>(d) * nwords + w) = bal;
+            if (bal) atomicAdd(&cnt[ri], __popcll(bal));
+        }
+    }
+    __syncthreads();
+    if (tid < kSpsRows && d0 + tid < ndm && cnt[tid] > 0) atomicAdd(&rowcount[d0 + tid], cnt[tid]);
+}
+
+// The screened detection. A wave takes kRunRows adjacent rows (trials) and a run of
+// consecutive tiles of 256 starts; lane l holds the four starts 4 l .. 4 l + 3 of each, so
+// that a width's prefixes are one aligned 16-byte LDS read (two where the width is not a
+// multiple of 4). A cell passes if some width's window sum reaches that width's smallest
+// passing sum (min_passing_sum), which is exactly the float64 rule best >= threshold; only
+// the cells that pass, with their 8 neighbours, are evaluated in float64 for the 3x3 peak
+// decision. The launcher takes this path only when every window sum is below 2^31.
+//
+// Nothing is shared between waves: the prefix sums of neighbouring rows are only needed
+// beside a passing cell, and are then built by the wave that has it. Up to a width of 256 a
+// tile's second 256 columns are the next tile's first: their prefix sums stay in registers,
+// and the columns after them are loaded while the tile is screened (STEP). Beyond that,
+// each tile is built by itself.
+//
+// The vector ALUs bound it: 3000 trials x 225,000 starts with widths 1, 2 .. 256 take 0.68 ms
+// (4 TB/s of plane). Tiles of 8 rows and 256 starts in work-groups, with a prefix for every
+// halo row, an LDS read per lane, width and start and the peak test beside the screen, took
+// 1.48 ms; 100 x 32,000 with 6 widths took 37.6 us against 16.8 now.
+//  - The peak test runs after the run's screen, on the mask words that the lanes hold, so
+//    that its registers are not live beside the screen's (with the test inside the loop over
+//    tiles, spilled registers made it 2.4 ms).
+//  - POW2 (widths 1, 2, 4 .. up to 256): distances are constants, two widths share one
+//    three-way maximum and no width needs a branch on its alignment: 0.68 ms against 0.91 ms.
+//  - Five waves per SIMD: with four 0.71 ms, with six (spilled registers) 0.85 ms.
+constexpr int kRunRows = 2;
+constexpr int kPow2Widths = 9;   // widths 1, 2, 4 .. 256
+constexpr int kCellsPerRound = 21;                       // cells of three lanes each
+constexpr uint64_t kRoundMask = 0x1249249249249249ull;   // their first lanes
+// LDS of one wave: the list of a row's passing cells, then prefix sums of three rows
+constexpr int kListBytes = 2 * kCellsPerRound * 4 + 8;
+static_assert(kListBytes % 16 == 0, "the prefix sums follow");
+__host__ __device__ inline int screen_lds(int wmax) { return kListBytes + prefix_bytes(wmax, kRunRows + 1); }
+
+// Orders a wave's LDS accesses for its lanes' reads of each other's writes.
+__device__ __forceinline__ void wave_lds_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+}
+
+template <bool STEP, bool POW2>
+__global__ __launch_bounds__(256, 5) void sps_screen_kernel(
+    const int32_t* __restrict__ dd, int64_t dd_pitch, int64_t dd_t0, int64_t dd_n, int64_t t_begin,
+    int64_t t_end, int64_t t_total, int32_t B, int32_t ndm, double threshold, SpsConst sc,
+    const double* __restrict__ norms, const uint32_t* __restrict__ smin_g, int32_t* __restrict__ rowcount,
+    uint32_t* __restrict__ mask, int64_t nwords, int32_t ntiles, int32_t nt, int32_t nruns) {
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int nw = sc.nw;
+    const int nq = prefix_groups(sc.wmax);
+    const int ps = prefix_row_stride(sc.wmax);
+    const int wave = __builtin_amdgcn_readfirstlane(static_cast<int>(threadIdx.x) >> 6), lane = threadIdx.x & 63;
+    uint32_t* const list = reinterpret_cast<uint32_t*>(smem + wave * screen_lds(sc.wmax));
+    uint8_t* const lds = smem + wave * screen_lds(sc.wmax) + kListBytes;
+    uint32_t* const pre = reinterpret_cast<uint32_t*>(lds + kPrefixHead);   // three rows with halo, of a passing cell
+    u32x4* const run = reinterpret_cast<u32x4*>(lds);                       // [kRunRows][nq] of the screened tile
+
+    const int item = static_cast<int>(blockIdx.x) * 4 + wave;
+    const int d0 = item / nruns * kRunRows;
+    const int b0 = item % nruns * nt, b1 = min(b0 + nt, ntiles);
+    if (d0 >= ndm) return;
+    const int wlane = lane < nw ? sc.widths[lane < kMaxWidths ? lane : 0] : 0;   // width of lane k
+    const int per_block = B / kSpsTile;                                          // B is a multiple of kSpsTile
+
+    __amdgpu_buffer_rsrc_t rsrc[kRunRows];
+    u32x4 q0[kRunRows], xn[kRunRows];   // prefix sums of the tile's first 256 columns, the next 256 columns
+    uint32_t carry[kRunRows];
+    {
+        const int64_t col = t_begin + static_cast<int64_t>(b0) * kSpsTile - dd_t0;
+        const int n = columns_left(dd_n, col, (b1 - b0 - 1) * kSpsTile + 4 * nq);
+#pragma unroll
+        for (int h = 0; h < kRunRows; ++h) {
+            rsrc[h] = row_buffer(dd, dd_pitch, ndm, d0 + h, col, n);
+            q0[h] = load_group(rsrc[h], lane);
+            xn[h] = load_group(rsrc[h], 64 + lane);
+            carry[h] = 0u;
+        }
+        if constexpr (STEP)
+#pragma unroll
+            for (int h = 0; h < kRunRows; ++h) q0[h] = scan_group(q0[h], carry[h]);
+    }
+    uint32_t words[kRunRows] = {};   // lane 8 k + i: mask word i of the run's tile k
+    // minus a width's smallest passing window sum (kNever if none): lane k of nsm, ns[k]
+    int nsm[kRunRows];
+    uint32_t ns[kRunRows][kPow2Widths];
+    int next = b0;              // first tile past the stat block of nsm
+#pragma unroll 1
+    for (int b = b0; b < b1; ++b) {
+        const int64_t tt0 = t_begin + static_cast<int64_t>(b) * kSpsTile;
+        if (b == next) {
+            const int j = b / per_block;
+            next = (j + 1) * per_block;
+#pragma unroll
+            for (int h = 0; h < kRunRows; ++h) {
+                uint32_t v = kNever;
+                if (lane < nw && d0 + h < ndm) v = smin_g[(static_cast<int64_t>(j) * ndm + d0 + h) * nw + lane];
+                nsm[h] = static_cast<int>(0u - v);
+                if constexpr (POW2)
+#pragma unroll
+                    for (int k = 0; k < kPow2Widths; ++k)
+                        ns[h][k] = static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm[h], k));
             }
         }
-        __syncthreads();
-        if (tid < kSpsRows && d0 + tid < ndm && cnt[tid] > 0) atomicAdd(&rowcount[d0 + tid], cnt[tid]);
-    } else {
-        // wave w screens inner rows w and w + 4; lane l holds starts 64 q + l, q < 4. A cell
-        // passes if some width's window sum reaches that width's smallest passing sum,
-        // which is exactly the float64 rule best >= threshold. The same lanes take the exact
-        // peak test of the cells that pass, so each row's mask words and count come from
-        // one wave.
-        // both rows in one width loop (row wave + 5 reads the prefix of row wave + 1 if it
-        // is past the last trial; its result is not used)
-        int32_t margin[2][4];   // max over widths of (window sum - smallest passing sum)
-        {
-            const uint32_t* pr0 = pre + (wave + 1) * ps + 1 + lane;   // prefix at start tt0 + 64 q + lane
-            const uint32_t* pr1 = d0 + wave + 4 < ndm ? pre + (wave + 5) * ps + 1 + lane : pr0;
-            uint32_t neg0[2][4];
+        // prefix sums of the tile
+        u32x4 q1[kRunRows];
+        if constexpr (STEP) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                neg0[0][q] = 0u - pr0[64 * q];
-                neg0[1][q] = 0u - pr1[64 * q];
-                asm volatile("" : "+v"(neg0[0][q]), "+v"(neg0[1][q]));   // keep each sum one three-way add
-                margin[0][q] = margin[1][q] = INT32_MIN;
+            for (int h = 0; h < kRunRows; ++h) {
+                q1[h] = scan_group(xn[h], carry[h]);
+                run[h * nq + lane] = q0[h];
+                if (64 + lane < nq) run[h * nq + 64 + lane] = q1[h];
             }
-            const int nsm0 = static_cast<int>(0u - smin[0]);   // lane k: minus width k's threshold
-            const int nsm1 = static_cast<int>(0u - smin[1]);
-#pragma unroll 3
-            for (int k = 0; k < sc.kfull; ++k) {
-                const int w = __builtin_amdgcn_readlane(wlane, k);
-                const uint32_t nsk0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm0, k));
-                const uint32_t nsk1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm1, k));
-                // sum - smin lies in (-2^31, 2^31): sums are below 2^31 and smin <= 2^31
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    margin[0][q] = max(margin[0][q], static_cast<int32_t>(pr0[64 * q + w] + neg0[0][q] + nsk0));
-                    margin[1][q] = max(margin[1][q], static_cast<int32_t>(pr1[64 * q + w] + neg0[1][q] + nsk1));
+            for (int h = 0; h < kRunRows; ++h) xn[h] = load_group(rsrc[h], 64 * (b - b0 + 2) + lane);
+        } else {
+#pragma unroll
+            for (int h = 0; h < kRunRows; ++h) {
+                carry[h] = 0u;
+                if (b > b0) q0[h] = load_group(rsrc[h], 64 * (b - b0) + lane);
+                q0[h] = scan_group(q0[h], carry[h]);
+                run[h * nq + lane] = q0[h];
+#pragma unroll 1
+                for (int u0 = 64; u0 < nq; u0 += 64) {
+                    const u32x4 q = scan_group(load_group(rsrc[h], 64 * (b - b0) + u0 + lane), carry[h]);
+                    if (u0 + lane < nq) run[h * nq + u0 + lane] = q;
                 }
             }
-            // widths of the decimated hierarchy: only starts on the width's grid count
-#pragma unroll 1
-            for (int k = sc.kfull; k < nw; ++k) {
-                const int w = __builtin_amdgcn_readlane(wlane, k);
-                const uint32_t nsk0 = static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm0, k));
-                const uint32_t nsk1 = static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm1, k));
-                const uint32_t sm = static_cast<uint32_t>(sc.smask[k]);
+        }
+        wave_lds_sync();
+        int32_t margin[kRunRows][4];   // max over widths of (window sum - smallest passing sum)
+        {
+            uint32_t neg[kRunRows][4];
+            const u32x4* const pr[kRunRows] = {run + lane, run + nq + lane};   // prefixes at the lane's starts
+#pragma unroll
+            for (int h = 0; h < kRunRows; ++h) {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
-                    if ((static_cast<uint32_t>(tt0 + 64 * q + lane) & sm) == 0) {
-                        margin[0][q] = max(margin[0][q], static_cast<int32_t>(pr0[64 * q + w] + neg0[0][q] + nsk0));
-                        margin[1][q] = max(margin[1][q], static_cast<int32_t>(pr1[64 * q + w] + neg0[1][q] + nsk1));
+                    neg[h][q] = 0u - q0[h][q];
+                    asm volatile("" : "+v"(neg[h][q]));   // keep each sum one three-way add
+                    margin[h][q] = INT32_MIN;
+                }
+            }
+            // sum - smin lies in (-2^31, 2^31): sums are below 2^31 and smin <= 2^31
+            auto over = [&](int h, uint32_t n, uint32_t x, int q) { return static_cast<int32_t>(x + neg[h][q] + n); };
+            if constexpr (POW2) {
+                // width 2^k, k < nw: the prefixes 2^k past the lane's starts are in its own group
+                // and the next one for k < 2, and whole groups at constant distances beyond; both
+                // rows go together, so that their LDS reads overlap
+                u32x4 y[kRunRows];
+#pragma unroll
+                for (int h = 0; h < kRunRows; ++h) y[h] = pr[h][1];
+                auto ahead = [&](auto K, int h) -> u32x4 {
+                    if constexpr (K == 0) return u32x4{q0[h][1], q0[h][2], q0[h][3], y[h][0]};
+                    else if constexpr (K == 1) return u32x4{q0[h][2], q0[h][3], y[h][0], y[h][1]};
+                    else if constexpr (K == 2) return y[h];
+                    else return pr[h][1 << (K - 2)];
+                };
+                auto single = [&](auto K) {
+                    if (K < sc.kfull) {
+                        u32x4 x[kRunRows];
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h) x[h] = ahead(K, h);
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q) margin[h][q] = max(over(h, ns[h][K], x[h][q], q), margin[h][q]);
+                    } else if (K < nw) {   // at starts that are multiples of smask + 1, a power of two, only
+                        const int sm = sc.smask[K];
+                        u32x4 x[kRunRows];
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h) x[h] = ahead(K, h);
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h) {
+                            const int32_t m = over(h, ns[h][K], x[h][0], 0);
+                            if (((4 * lane) & sm) == 0) margin[h][0] = max(m, margin[h][0]);
+                            if (sm == 1) margin[h][2] = max(over(h, ns[h][K], x[h][2], 2), margin[h][2]);
+                        }
+                    }
+                };
+                auto two = [&](auto K) {
+                    constexpr std::integral_constant<int, K + 1> K1{};
+                    if (K1 < sc.kfull) {
+                        u32x4 x0[kRunRows], x1[kRunRows];
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h) x0[h] = ahead(K, h), x1[h] = ahead(K1, h);
+#pragma unroll
+                        for (int h = 0; h < kRunRows; ++h)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
+                                margin[h][q] = max(max(over(h, ns[h][K], x0[h][q], q), over(h, ns[h][K1], x1[h][q], q)),
+                                                   margin[h][q]);
+                    } else {
+                        single(K);
+                        single(K1);
+                    }
+                };
+                two(std::integral_constant<int, 0>{});
+                two(std::integral_constant<int, 2>{});
+                two(std::integral_constant<int, 4>{});
+                two(std::integral_constant<int, 6>{});
+                single(std::integral_constant<int, 8>{});
+                static_assert(kPow2Widths == 9, "the widths above");
+            } else {
+            auto nsmin = [&](int h, int k) { return static_cast<uint32_t>(__builtin_amdgcn_readlane(nsm[h], k)); };
+            // one width whose prefixes, entries 4 l + w .. + 3, start A entries into an aligned
+            // 16 bytes (the branch on A is uniform and holds the whole update, so that nothing is
+            // copied); STRIDED: a width of the decimated hierarchy, whose starts off the width's
+            // grid do not count
+            auto one = [&](auto A, auto STRIDED, int k, int w) {
+                const uint32_t sm = STRIDED ? static_cast<uint32_t>(sc.smask[k]) : 0u;
+#pragma unroll
+                for (int h = 0; h < kRunRows; ++h) {
+                    const u32x4 x = pr[h][w >> 2];
+                    u32x4 y = x;
+                    if constexpr (A != 0) y = pr[h][(w >> 2) + 1];
+                    const uint32_t n = nsmin(h, k);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        const int32_t m = over(h, n, q + A < 4 ? x[(q + A) & 3] : y[(q + A) & 3], q);
+                        if (!STRIDED || (static_cast<uint32_t>(tt0 + 4 * lane + q) & sm) == 0) margin[h][q] = max(m, margin[h][q]);
                     }
                 }
-            }
-        }
-#pragma unroll 1
-        for (int h = 0; h < 2; ++h) {
-            const int ri = wave + 4 * h, r = ri + 1;
-            const int d = d0 + ri;
-            if (d >= ndm) break;
-            uint32_t pass = 0;
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                if ((h ? margin[1][q] : margin[0][q]) >= 0 && tt0 + 64 * q + lane < tile_end) pass |= 1u << q;
-            int pop = 0;
-#pragma unroll 1
-            for (int q = 0; q < 4; ++q) {
-                bool ok = false;
-                if ((pass >> q) & 1u) {
-                    auto val = [&](int rr_, int cc) {
-                        const int dr = d0 - 1 + rr_;
-                        const int64_t tr = tt0 - 1 + cc;
-                        return exact_best(pre, ps, nj, d0, sc, rr_, cc, dr >= 0 && dr < ndm && tr >= lo && tr < hi,
-                                          static_cast<uint32_t>(tr));
-                    };
-                    const int c0 = 64 * q + lane + 1;
-                    const double x = val(r, c0);
-                    ok = x >= threshold && x > val(r - 1, c0 - 1) && x > val(r - 1, c0) && x > val(r - 1, c0 + 1) &&
-                         x > val(r, c0 - 1) && x >= val(r, c0 + 1) && x >= val(r + 1, c0 - 1) &&
-                         x >= val(r + 1, c0) && x >= val(r + 1, c0 + 1);
+            };
+            auto any = [&](auto STRIDED, int k, int w) {
+                switch (w & 3) {
+                    case 0: one(std::integral_constant<int, 0>{}, STRIDED, k, w); break;
+                    case 1: one(std::integral_constant<int, 1>{}, STRIDED, k, w); break;
+                    case 2: one(std::integral_constant<int, 2>{}, STRIDED, k, w); break;
+                    default: one(std::integral_constant<int, 3>{}, STRIDED, k, w);
                 }
-                const uint64_t bal = __ballot(ok);
-                if (lane == 0)
-                    *reinterpret_cast<uint64_t*>(mask + static_cast<int64_t>(d) * nwords + (tt0 - t_begin) / 32 + 2 * q) = bal;
-                pop += __popcll(bal);
+            };
+#pragma unroll 1
+            for (int k = 0; k < sc.kfull;) {
+                const int w0 = __builtin_amdgcn_readlane(wlane, k);
+                const int w1 = k + 1 < sc.kfull ? __builtin_amdgcn_readlane(wlane, k + 1) : 1;
+                if (((w0 | w1) & 3) == 0) {   // two aligned widths: one three-way maximum for both
+#pragma unroll
+                    for (int h = 0; h < kRunRows; ++h) {
+                        const u32x4 x0 = pr[h][w0 >> 2], x1 = pr[h][w1 >> 2];
+                        const uint32_t n0 = nsmin(h, k), n1 = nsmin(h, k + 1);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            margin[h][q] = max(max(over(h, n0, x0[q], q), over(h, n1, x1[q], q)), margin[h][q]);
+                    }
+                    k += 2;
+                } else {
+                    any(std::false_type{}, k, w0);
+                    ++k;
+                }
             }
-            if (lane == 0 && pop > 0) atomicAdd(&rowcount[d], pop);
+#pragma unroll 1
+            for (int k = sc.kfull; k < nw; ++k) any(std::true_type{}, k, __builtin_amdgcn_readlane(wlane, k));
+            }
         }
+        const int nvalid = static_cast<int>(min<int64_t>(kSpsTile, t_end - tt0)) - 4 * lane;   // of the lane's starts
+#pragma unroll
+        for (int h = 0; h < kRunRows; ++h) {
+            if (__ballot(max(max(margin[h][0], margin[h][1]), max(margin[h][2], margin[h][3])) >= 0) != 0) {
+                uint32_t pass = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) pass |= static_cast<uint32_t>(margin[h][q] >= 0 && q < nvalid) << q;
+                uint32_t word = pass << (4 * (lane & 7));   // lanes 8 i .. 8 i + 7: word i
+                word |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(word), 1, 64));
+                word |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(word), 2, 64));
+                word |= static_cast<uint32_t>(__shfl_xor(static_cast<int>(word), 4, 64));
+                word = static_cast<uint32_t>(__shfl(static_cast<int>(word), 8 * (lane & 7), 64));
+                if (lane >> 3 == b - b0) words[h] = word;
+            }
+        }
+        wave_lds_sync();   // the next tile overwrites the prefix sums
+        if constexpr (STEP)
+#pragma unroll
+            for (int h = 0; h < kRunRows; ++h) q0[h] = q1[h];
+    }
+    // the exact peak test of the cells that pass, in place of their bits
+#pragma unroll 1
+    for (int h = 0; h < kRunRows; ++h) {
+        const int d = d0 + h;
+        if (d >= ndm) break;
+        uint32_t word = h ? words[1] : words[0];
+        int found = 0;
+        const uint64_t some = __ballot(word != 0);
+#pragma unroll 1
+        for (int k = 0; k < b1 - b0; ++k) {
+            if (((some >> (8 * k)) & 0xff) == 0) continue;
+            const int64_t tt0 = t_begin + static_cast<int64_t>(b0 + k) * kSpsTile;
+            const int64_t tile_end = min(tt0 + kSpsTile, t_end);
+            const double* nj = norms + static_cast<int64_t>((b0 + k) / per_block) * ndm * (2 * nw);
+            const uint32_t nibble = static_cast<uint32_t>(__shfl(static_cast<int>(word), 8 * k + (lane >> 3), 64)) >> (4 * (lane & 7));
+            if (lane >> 3 == k) word = 0;
+            uint64_t pass[4];   // lanes whose start q passes
+            int npass = 0;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                pass[q] = __ballot((nibble >> q) & 1u);
+                npass += __popcll(pass[q]);
+            }
+            const int64_t lo = max(tt0 - 1, static_cast<int64_t>(0));
+            const int64_t hi = (t_total < 0 || tile_end < t_total) ? tile_end + 1 : tile_end;  // best valid in [lo, hi)
+            const int dt[3] = {d - 1, d, d + 1};
+            uint32_t* const prow[3] = {pre, pre + ps, pre + 2 * ps};
+            const RowNorm norm[3] = {load_norm(nj, d - 1, d > 0, nw, lane), load_norm(nj, d, true, nw, lane),
+                                     load_norm(nj, d + 1, d + 1 < ndm, nw, lane)};
+            tile_prefix<3>(dd, dd_pitch, dd_n, ndm, tt0 - dd_t0, nq, dt, prow, lane);
+            const double ninf = -__builtin_huge_val();
+            // a peak at start s of the tile
+            auto peaks = [&](uint64_t lanes, int s) {
+                found += __popcll(lanes);
+                for (; lanes; lanes &= lanes - 1) {
+                    const int sl = __builtin_amdgcn_readlane(s, __ffsll(static_cast<unsigned long long>(lanes)) - 1);
+                    if (lane == 8 * k + (sl >> 5)) word |= 1u << (sl & 31);
+                }
+            };
+            if (npass <= 2 * kCellsPerRound) {
+                // few cells pass: they are listed, and three lanes take one cell, one column of
+                // its 3 x 3 neighbourhood each
+                int below = 0;
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {
+                    if ((pass[q] >> lane) & 1u) list[below + __popcll(pass[q] & ((1ull << lane) - 1))] = 4 * lane + q;
+                    below += __popcll(pass[q]);
+                }
+                wave_lds_sync();
+#pragma unroll 1
+                for (int i0 = 0; i0 < npass; i0 += kCellsPerRound) {
+                    const int i = lane / 3, e = lane - 3 * i;             // cell of the round, column - 1
+                    const bool have = i < kCellsPerRound && i0 + i < npass;
+                    const int s = have ? static_cast<int>(list[i0 + i]) : 0;
+                    const int64_t tr = tt0 + s - 1 + e;
+                    const uint32_t* const p0 = pre + s + e;
+                    const uint32_t* const pr[3][1] = {{p0}, {p0 + ps}, {p0 + 2 * ps}};
+                    const uint32_t t[1] = {static_cast<uint32_t>(tr)};
+                    double v[3][1] = {};
+                    exact_best<3, 1>(pr, t, norm, sc, wlane, v);
+                    const bool in = tr >= lo && tr < hi;
+                    const double up = in && d > 0 ? v[0][0] : ninf, mid = in ? v[1][0] : ninf;
+                    const double down = in && d + 1 < ndm ? v[2][0] : ninf;
+                    const double x = __shfl(mid, 3 * i + 1, 64);          // the cell's own S/N
+                    const bool beside = e == 0 ? x > mid : (e == 1 ? x >= threshold : x >= mid);
+                    uint64_t ok = __ballot(have && x > up && beside && x >= down);
+                    ok &= ok >> 1 & ok >> 2 & kRoundMask;
+                    peaks(ok, s);
+                }
+            } else {
+                // all starts of three rows, four a lane, the halo columns in the outer lanes
+                wave_lds_sync();
+                double x[4];
+                bool ok[4];
+#pragma unroll 1
+                for (int e = 0; e < 3; ++e) {
+                    const int i = e == 0 ? 1 : e == 1 ? 0 : 2;            // the cells' own row first
+                    const RowNorm rn[1] = {e == 0 ? norm[1] : e == 1 ? norm[0] : norm[2]};
+                    const uint32_t* pr[1][4];
+                    uint32_t t[4];
+                    double v[1][4] = {};
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        pr[0][q] = pre + i * ps + 4 * lane + q + 1;
+                        t[q] = static_cast<uint32_t>(tt0 + 4 * lane + q);
+                    }
+                    exact_best<1, 4>(pr, t, rn, sc, wlane, v);
+                    const int ch = lane < 32 ? 0 : kHaloCols - 1;
+                    const uint32_t* const ph[1][1] = {{pre + i * ps + ch}};
+                    const uint32_t th[1] = {static_cast<uint32_t>(tt0 - 1 + ch)};
+                    double vh[1][1] = {};
+                    exact_best<1, 1>(ph, th, rn, sc, wlane, vh);
+                    const bool in_row = d - 1 + i >= 0 && d - 1 + i < ndm;
+                    auto valid = [&](double u, int64_t tr) { return in_row && tr >= lo && tr < hi ? u : ninf; };
+                    double m[6];                                          // columns 4 lane - 1 .. 4 lane + 4
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) m[1 + q] = valid(v[0][q], tt0 + 4 * lane + q);
+                    vh[0][0] = valid(vh[0][0], tt0 - 1 + ch);
+                    m[0] = __shfl_up(m[4], 1, 64);
+                    m[5] = __shfl_down(m[1], 1, 64);
+                    if (lane == 0) m[0] = vh[0][0];
+                    if (lane == 63) m[5] = vh[0][0];
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) {
+                        if (e == 0) {
+                            x[q] = m[1 + q];
+                            ok[q] = ((pass[q] >> lane) & 1u) != 0 && x[q] >= threshold && x[q] > m[q] && x[q] >= m[2 + q];
+                        } else if (e == 1) {
+                            ok[q] = ok[q] && x[q] > m[q] && x[q] > m[1 + q] && x[q] > m[2 + q];
+                        } else {
+                            ok[q] = ok[q] && x[q] >= m[q] && x[q] >= m[1 + q] && x[q] >= m[2 + q];
+                        }
+                    }
+                }
+#pragma unroll
+                for (int q = 0; q < 4; ++q) peaks(__ballot(ok[q]), 4 * lane + q);
+            }
+            wave_lds_sync();   // the next tile overwrites the prefix sums
+        }
+        if (lane < 8 * (b1 - b0)) mask[static_cast<int64_t>(d) * nwords + static_cast<int64_t>(b0) * (kSpsTile / 32) + lane] = word;
+        if (lane == 0 && found > 0) atomicAdd(&rowcount[d], found);
     }
 }
 
@@ -568,6 +901,13 @@ __global__ __launch_bounds__(256) void sps_emit_kernel(
     }
 }
 
+// Tiles of a run of the screened detection: as few as still let all waves be resident at once
+// (five per SIMD), at most 8 (the mask words of a row's run are one dword per lane). 3000 x
+// 225,000 cells: 0.69 ms with 8, 0.78 with 4, 1.54 with 1; 100 x 32,000 cells: 16.8 us with 2
+// (this rule), 17.6 with 1 or 3.
+constexpr int64_t kScreenWaves = 5120;
+constexpr int64_t kMaxRun = 8;
+
 size_t align256(size_t x) { return (x + 255) & ~static_cast<size_t>(255); }
 
 struct WorkLayout {
@@ -626,11 +966,29 @@ int launch_single_pulse(const aa_plan_s* p, const int32_t* d_dd, int64_t dd_pitc
         return fail(AA_EINVAL, "aa_single_pulse: too many detection tiles for one launch");
     // the integer screen compares window sums below 2^31
     const bool screen = !d_best && static_cast<uint64_t>(p->nchan) * 255u * static_cast<uint64_t>(p->wmax) < (1ull << 31);
-    const size_t lds = static_cast<size_t>(detect_lds(p->wmax, p->nwidths, !screen).total);
-    hipLaunchKernelGGL(screen ? sps_detect_kernel<false> : sps_detect_kernel<true>,
-                       dim3(static_cast<unsigned>(L.ntiles), rowblocks), dim3(256), lds, stream,
-                       d_dd, dd_pitch, dd_t0, dd_n, t_begin, t_end, t_total, p->stat_block, p->ndm,
-                       static_cast<double>(p->threshold), sc, norms, smin, rowcount, mask, L.nwords, d_best, best_pitch);
+    if (screen) {
+        const int64_t rowpairs = (p->ndm + kRunRows - 1) / kRunRows;
+        const int64_t nt = std::max<int64_t>(1, std::min<int64_t>(kMaxRun, (L.ntiles * rowpairs + kScreenWaves - 1) / kScreenWaves));
+        const int64_t nruns = (L.ntiles + nt - 1) / nt;
+        // widths 1, 2, 4 .. 256 (with or without the decimated hierarchy) have their own kernel:
+        // 0.68 ms against 0.91 ms of the general one for 3000 x 225,000 cells, 0.13 against
+        // 0.18 ms for 1000 x 100,000 with the hierarchy; past a width of 256 a tile's prefix
+        // sums no longer fit two groups of 256 columns
+        bool pow2 = p->nwidths <= kPow2Widths;
+        for (int k = 0; k < p->nwidths; ++k) pow2 = pow2 && p->widths[k] == 1 << k;
+        hipLaunchKernelGGL(pow2 ? (sps_screen_kernel<true, true>)
+                                : p->wmax <= kSpsTile ? (sps_screen_kernel<true, false>) : (sps_screen_kernel<false, false>),
+                           dim3(static_cast<unsigned>((nruns * rowpairs + 3) / 4)), dim3(256),
+                           static_cast<size_t>(4 * screen_lds(p->wmax)), stream, d_dd, dd_pitch, dd_t0, dd_n, t_begin, t_end,
+                           t_total, p->stat_block, p->ndm, static_cast<double>(p->threshold), sc, norms, smin, rowcount,
+                           mask, L.nwords, static_cast<int32_t>(L.ntiles), static_cast<int32_t>(nt),
+                           static_cast<int32_t>(nruns));
+    } else {
+        hipLaunchKernelGGL(sps_best_kernel, dim3(static_cast<unsigned>(L.ntiles), rowblocks), dim3(256),
+                           static_cast<size_t>(best_lds(p->wmax)), stream, d_dd, dd_pitch, dd_t0, dd_n, t_begin, t_end,
+                           t_total, p->stat_block, p->ndm, static_cast<double>(p->threshold), sc, norms, rowcount, mask,
+                           L.nwords, d_best, best_pitch);
+    }
     AA_HIP(hipGetLastError());
     hipLaunchKernelGGL(sps_emit_kernel, dim3(static_cast<unsigned>(p->ndm)), dim3(256), 0, stream, d_dd, dd_pitch,
                        dd_t0, t_begin, p->stat_block, p->ndm, sc, norms, rowcount, mask, L.nwords, d_cand, cap,

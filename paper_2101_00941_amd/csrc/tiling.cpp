@@ -513,7 +513,14 @@ bool strip_runs(const StripBlock& b, int spread_max, std::vector<StripRun>& runs
     return true;
 }
 
-// Estimated cycles of a block's work per time tile: see the cost rule at build_strip_tables.
+// Estimated cycles of a block's work per time tile, by which a block takes 8 channels x 4
+// residuals or 4 x 8: a substep costs its staged rows (60 or 40) and 150 per strip of the
+// busiest SIMD, a run's flush 280 per strip and 300. Eight channels a matrix operation halve
+// the matrix work, but four residuals end a run of channels sooner. Measured with either
+// shape forced (8 x 4 / 4 x 8, ms): ranges of trials of a survey plan, from the slowest drift
+// to the steepest, 3.57 / 5.66, 4.03 / 5.97, 4.64 / 6.16, 5.07 / 5.50, 10.22 / 8.97; 100 trials
+// of a 2^18-sample chunk of 128 channels 0.207 / 0.157; 333 trials of 1001 channels 0.982 /
+// 0.624. The estimate picks the faster one in all of them.
 double strip_cost(const std::vector<StripRun>& runs, int cps, int tile) {
     double c = 0.0;
     for (const StripRun& r : runs) {

@@ -19,6 +19,12 @@
 //    step k the contracting waves run the matrix ops of step k on operands already in
 //    registers and read those of step k + 1, while the staging waves store step k + 2. So no
 //    LDS latency is waited for within a step.
+// Measured against the 4 x 8 step kernel with 1024-sample tiles (variant 25): 4096 channels x
+// 2^20 samples, 3000 trials 106 ms (230 ms; 117 T byte-adds/s), 1500 trials of a 2^17-sample
+// chunk 5.8 ms (14.1 ms), 333 trials of 1001 channels x 77,777 samples 0.60 ms (0.96 ms). On the
+// chunk matrix cores are busy 31% of the SIMDs' cycles and other vector instructions 38%: about
+// ten go with a matrix operation, most of them window shifts; waits for the step barrier and
+// for operands make up the rest.
 #include "dedisp_device.h"
 
 namespace aa {
@@ -48,7 +54,11 @@ __device__ __forceinline__ void step_barrier() {
 // + j of t', trial m, and goes to t = t' - e; rows outside [0, TILE) are clamped to the
 // discarded rows -1 and TILE. A wave's 64 adds hit 32 banks twice each, for any e. The LDS
 // takes one add instruction per 4.2 cycles (measured, and the same for stores), which hides
-// the clamps of the four SIMDs.
+// the clamps of the four SIMDs: strips that lie inside the tile, added without clamps in a
+// branch of their own, gained nothing (100 trials of a 2^18-sample chunk 0.158 ms, 0.149 so).
+// Address and add are one block of instructions with one register between them: left to the
+// compiler, the addresses of many adds were formed ahead, and the batch kernel, whose item loop
+// holds a few registers more, spilled (five beams 6.2 ms, 7.8 that way).
 template <int TILE>
 __device__ __forceinline__ void strip_flush(i32x16 (&acc)[4], int q, int m, int h, int e, uint32_t row0) {
     const int lo = static_cast<int>(row0) + 4 * m - 128, hi = static_cast<int>(row0) + 4 * m + 128 * TILE;
@@ -57,8 +67,11 @@ __device__ __forceinline__ void strip_flush(i32x16 (&acc)[4], int q, int m, int 
     for (int i = 0; i < 16; ++i)
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int at = min(max(base + 128 * (4 * (8 * (i >> 2) + (i & 3)) + j), lo), hi);
-            asm volatile("ds_add_u32 %0, %1" ::"v"(at), "v"(acc[j][i]) : "memory");
+            int at;
+            asm volatile("v_add_u32 %0, %1, %2\n\tv_med3_i32 %0, %0, %3, %4\n\tds_add_u32 %0, %5"
+                         : "=&v"(at)
+                         : "n"(128 * (4 * (8 * (i >> 2) + (i & 3)) + j)), "v"(base), "v"(lo), "v"(hi), "v"(acc[j][i])
+                         : "memory");
         }
 #pragma unroll
     for (int j = 0; j < 4; ++j) acc[j] = i32x16{};

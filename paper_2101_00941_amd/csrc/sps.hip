@@ -1058,8 +1058,8 @@ __global__ __launch_bounds__(256) void sps_emit_kernel(
 
 // Tiles of a run of the screened detection: as few as still let all waves be resident at once
 // (five per SIMD), at most 8 (the mask words of a row's run are one dword per lane). 3000 x
-// 225,000 cells: 0.69 ms with 8, 0.78 with 4, 1.54 with 1; 100 x 32,000 cells: 16.8 us with 2
-// (this rule), 17.6 with 1 or 3.
+// 225,000 cells: 0.69 ms with 8, 0.78 with 4, 1.54 with 1, and 0.73 with 16 (two dwords a lane);
+// 100 x 32,000 cells: 16.8 us with 2 (this rule), 17.6 with 1 or 3.
 constexpr int64_t kScreenWaves = 5120;
 constexpr int64_t kMaxRun = 8;
 

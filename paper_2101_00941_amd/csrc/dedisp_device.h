@@ -41,6 +41,18 @@ typedef __attribute__((address_space(3))) void lds_void;
 typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
 typedef int32_t i32x16 __attribute__((ext_vector_type(16)));
 
+// Waits until the results of the matrix operations before it may be read by inline assembly.
+// v_mfma_i32_32x32x32_i8 takes eight passes, and 12 wait states must pass before an LDS or
+// vector instruction reads its result. The hardware does not hold the reader back: the compiler
+// puts the wait in front of its own instructions, and none in front of an asm statement. Each
+// tile goes through an asm statement of its own, so that no matrix operation moves past the wait.
+template <int N>
+__device__ __forceinline__ void wait_matrix_results(i32x16 (&acc)[N]) {
+#pragma unroll
+    for (int j = 1; j < N; ++j) asm volatile("" : "+v"(acc[j]));
+    asm volatile("s_nop 11" : "+v"(acc[0])::"memory");
+}
+
 // The batched persistent launch: a work-group pulls item indexes from the device counter
 // until they run out (every work-group reaches that exit) and runs tile(args, block, t0) of
 // the item's beam, found by binary search over item_begin. Consecutive items are adjacent

@@ -575,7 +575,9 @@ __device__ __forceinline__ void mfma_block(const MfmaCtx& cx, uint8_t* lds, int 
     // flight (they write other LDS bytes); the barrier after the tile's last block
     // orders them before the final read. A tile whose rows land in [0, TILE) for every
     // e in [0, max e] adds with immediate offsets and no checks. (e[m] and max e are the
-    // same in every record of the block; the caller reads them from its first step.)
+    // same in every record of the block; the caller reads them from its first step.) The
+    // asm statements hide the accumulators' use from the compiler, so the wait is stated.
+    wait_matrix_results(acc);
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
         const int q = cx.wave + W * j;

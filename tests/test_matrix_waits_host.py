@@ -105,7 +105,7 @@ def _unwaited(lines):
     return bad, len(reads)
 
 
-@pytest.mark.parametrize("source", ["strip.hip"])
+@pytest.mark.parametrize("source", ["strip.hip", "dedisp.hip"])
 def test_asm_reads_of_matrix_results_wait(source, tmp_path):
     if not os.path.exists(build.HIPCC) and not shutil.which("hipcc"):
         pytest.skip("hipcc not available")

@@ -424,10 +424,10 @@ int build_quad_tables(const aa_plan_s* p, int tile, int chunks, std::vector<DmBl
     return AA_OK;
 }
 
-// Tables of the strip variant (layout 8, see aa_internal.h). A DM block is the longest
-// range of up to 32 trials (tried from 32 down) whose every substep has a residual range
-// below R and whose every run's spread of E is at most strip_spread(tile). A single trial
-// always qualifies (f = 0). Runs are greedy.
+// Tables of the strip variant (layout 8, see aa_internal.h). A DM block is the first range of
+// trials, tried from 32 (or all that are left) down in steps of 4, from 16 in steps of 2 and from
+// 8 of 1, whose every substep has a residual range below R and whose every run's spread of E is
+// at most strip_spread(tile). A single trial always qualifies (f = 0). Runs are greedy.
 namespace {
 
 struct StripRun {
@@ -513,6 +513,40 @@ bool strip_runs(const StripBlock& b, int spread_max, std::vector<StripRun>& runs
     return true;
 }
 
+// Whether a block's first and last trial alone show, at the ends of the band, that strip_runs
+// would refuse it: residuals are widest in the last substeps, and E' in the first and the last.
+// A run's E' lies at most R - 1 below a substep's, and the delays are monotone over the band but
+// for their rounding, so that the skews, taken from the ends here, are off by less than 8 each.
+// Most lengths tried for a steep block end here: a plan of 500 trials 20 apart over 1024 channels
+// is made in 14 ms, with the whole block's ranges for every length in 249 ms.
+bool strip_too_long(const aa_plan_s* p, int first, int count, int cps, int spread_max) {
+    const int nchan = p->nchan, R = 32 / cps, nsub = (nchan + cps - 1) / cps;
+    const int32_t* ref = &p->shifts[static_cast<size_t>(first + count / 2) * nchan];
+    int32_t head[2], tail[2];
+    for (int k = 0; k < 2; ++k) {
+        const int32_t* sd = &p->shifts[static_cast<size_t>(first + (k ? count - 1 : 0)) * nchan];
+        int32_t l, h;
+        auto range = [&](int s) {
+            l = INT32_MAX;
+            h = INT32_MIN;
+            for (int c = s * cps; c < std::min(s * cps + cps, nchan); ++c) {
+                l = std::min(l, sd[c] - ref[c]);
+                h = std::max(h, sd[c] - ref[c]);
+            }
+        };
+        for (int s = std::max(0, nsub - 2); s < nsub; ++s) {
+            range(s);
+            if (h - l > R - 1) return true;
+        }
+        tail[k] = l;
+        range(0);
+        head[k] = l;
+    }
+    const int32_t mid0 = head[0] + (tail[0] - head[0]) / 2, mid1 = head[1] + (tail[1] - head[1]) / 2;
+    const int32_t spread = std::max(std::abs((head[0] - mid0) - (head[1] - mid1)), std::abs((tail[0] - mid0) - (tail[1] - mid1)));
+    return spread > spread_max + R - 1 + 16;
+}
+
 // Estimated cycles of a block's work per time tile, by which a block takes 8 channels x 4
 // residuals or 4 x 8: a substep costs its staged rows (60 or 40) and 150 per strip of the
 // busiest SIMD, a run's flush 280 per strip and 300. Eight channels a matrix operation halve
@@ -551,8 +585,10 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
             if (shape != 0 && cps != shape) continue;
             int count = std::min(32, p->ndm - d0);
             for (;;) {
-                strip_ranges(p, d0, count, cps, sb);
-                if (strip_runs(sb, strip_spread(tile), runs)) break;
+                if (!strip_too_long(p, d0, count, cps, strip_spread(tile))) {
+                    strip_ranges(p, d0, count, cps, sb);
+                    if (strip_runs(sb, strip_spread(tile), runs)) break;
+                }
                 if (count == 1) return fail(AA_EINVAL, "strip tiling: a single trial does not fit");
                 count -= count > 16 ? 4 : count > 8 ? 2 : 1;
             }

@@ -133,9 +133,11 @@ int aa_dedisperse(aa_plan_t plan, const uint8_t* d_in, int64_t in_pitch, int64_t
  * and must not run concurrently with compute calls on the same plan.
  *   aa_variant_count()            number of variants
  *   aa_variant_info(v, out)       shape of variant v
- *   aa_plan_set_variant(plan, v)  prepare v and use it for aa_dedisperse (a new plan uses
- *                                 variant 12, the i8 matrix-core strip kernel)
- *   aa_plan_get_variant(plan, v)  variant in use
+ *   aa_plan_set_variant(plan, v)  prepare v and use it for every launch of the plan (a new
+ *                                 plan uses variant 12, the i8 matrix-core strip kernel,
+ *                                 and variant 25, a step kernel, for the launches that it
+ *                                 is estimated to end sooner: few channels, trials or tiles)
+ *   aa_plan_get_variant(plan, v)  variant in use (12 for a new plan)
  *   aa_autotune(...)              time every variant on the caller's buffers (reps runs
  *                                 each, HIP events on `stream`), select the fastest,
  *                                 and write the per-variant mean ms to ms_out

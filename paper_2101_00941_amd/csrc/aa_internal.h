@@ -170,6 +170,7 @@ inline bool variant_takes_pitch(int variant, int64_t in_pitch) {
     return kDedispVariants[variant].layout != 7 || in_pitch <= kQuadMaxPitch;
 }
 constexpr int kDefaultDedispVariant = 12;   // i8 matrix cores, strip kernel
+constexpr int kSmallDedispVariant = 25;     // the step kernel, for launches that launch_variant gives to it
 
 // Single-pulse-search tiling: a work-group covers kSpsRows DM rows and kSpsTile starts.
 constexpr int kSpsTile = 256;
@@ -204,6 +205,8 @@ struct DedispTables {
     uint8_t* d_pad = nullptr;        // layouts 4-6: one staged row of 0x80 bytes (padded channels)
     int split = -1;                  // layout 6: first trial of the 4-channel blocks
     int32_t span = 0;                // layout 8: largest span of a block's skews
+    double wg_us = 0.0, wg_max_us = 0.0;   // variants of launch_variant: estimated time of a work-group,
+                                           // mean and largest over the blocks
 };
 
 // Arguments of one dedispersion launch (one beam), passed by value or from a device table.
@@ -238,6 +241,7 @@ struct aa_plan_s {
     // dedispersion tiling tables, one set per kernel variant that has been prepared
     aa::DedispTables tables[aa::kNumDedispVariants];
     int variant = aa::kDefaultDedispVariant;   // variant used by aa_dedisperse
+    bool variant_chosen = false;               // set or tuned by the caller
     // device copies (uploaded once at plan time)
     int device = -1;
     int32_t* d_shifts = nullptr;
@@ -247,6 +251,11 @@ struct aa_plan_s {
 namespace aa {
 // Builds (host) and uploads (device, unless the plan is host-only) the tables of a variant.
 int prepare_variant(aa_plan_s* p, int variant);
+// Prepares what launches of a new plan use: the default variant, and for a plan whose launches
+// may be small the step kernel beside it.
+int prepare_default(aa_plan_s* p);
+// The variant that a launch over n_out output samples uses.
+int launch_variant(const aa_plan_s* p, int64_t n_out);
 // Host tables of the matrix-core variants: DM blocks, 16-aligned staged-row starts
 // [nblk][nchan_pad] and the per-step records [nblk][nchan_pad / cps][record size], with
 // nchan_pad = nchan rounded up to cps channels.

@@ -1096,5 +1096,6 @@ extern "C" int aa_dedisperse(aa_plan_t p, const uint8_t* d_in, int64_t in_pitch,
         return fail(AA_EINVAL, "aa_dedisperse: d_in and in_pitch must be multiples of 16 bytes");
     if ((reinterpret_cast<uintptr_t>(d_out) & 15) || (out_pitch & 3) || out_pitch < n_in - p->maxshift)
         return fail(AA_EINVAL, "aa_dedisperse: d_out must be 16-byte aligned, out_pitch a multiple of 4 and >= n_out");
-    return launch_dedisperse(p, p->variant, d_in, in_pitch, n_in, d_out, out_pitch, static_cast<hipStream_t>(stream));
+    return launch_dedisperse(p, launch_variant(p, n_in - p->maxshift), d_in, in_pitch, n_in, d_out, out_pitch,
+                             static_cast<hipStream_t>(stream));
 }

@@ -182,7 +182,7 @@ extern "C" int aa_plan(const aa_plan_desc_t* desc, aa_plan_t* out) {
         }
     }
     {
-        const int rc = prepare_variant(p, p->variant);
+        const int rc = prepare_default(p);
         if (rc != AA_OK) {
             free_device(p);
             delete p;

@@ -660,6 +660,12 @@ int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBl
 }
 
 namespace {
+// Adds a block's estimated work-group time (launch_variant) to its tables.
+void add_estimate(DedispTables& t, size_t nblk, double us) {
+    t.wg_us += us / static_cast<double>(nblk);
+    t.wg_max_us = std::max(t.wg_max_us, us);
+}
+
 int prepare_strip(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     std::vector<DmBlock> blocks;
     std::vector<int32_t> rs;
@@ -669,10 +675,27 @@ int prepare_strip(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     t.bd = 32;
     t.nchan_pad = strip_nchan_pad(p->nchan);
     t.max_row = 0;
-    for (const DmBlock& b : blocks) t.span = std::max(t.span, b.span);
+    // estimated work-group time, from the substeps, strips and runs of the info dwords
+    const int K = t.nchan_pad / 8;
+    for (const DmBlock& b : blocks) {
+        t.span = std::max(t.span, b.span);
+        const uint32_t* info = &rec[static_cast<size_t>(b.rec256) * 64 + static_cast<size_t>(K) * 64];
+        int64_t strips = 0, runs = 0, flushed = 0;
+        for (int k = 0; k < (p->nchan + 7) / 8; ++k)
+            for (int u = 0; u < 8 / b.cps; ++u) {
+                const int n = static_cast<int>((info[k] >> (2 + 4 * u)) & 15u) + 1;
+                strips += n;
+                if ((info[k] >> u) & 1u) {
+                    ++runs;
+                    flushed += n;
+                }
+            }
+        add_estimate(t, blocks.size(), 4.06 + 0.79 * (t.nchan_pad / 16) + 0.0073 * strips +
+                                             0.43 * runs + 0.074 * flushed + 0.116 * b.count);
+    }
     t.blocks = blocks;
     if (p->device >= 0) {
-                int rc = upload(&t.d_blocks, blocks);
+        int rc = upload(&t.d_blocks, blocks);
         if (rc == AA_OK) rc = upload(&t.d_base, rs);
         if (rc == AA_OK) rc = upload(reinterpret_cast<uint32_t**>(&t.d_offs), rec);
         if (rc != AA_OK) return rc;
@@ -708,6 +731,23 @@ int prepare_mfma(const aa_plan_s* p, const DedispVariant& V, DedispTables& t, in
     t.nchan_pad = cps == 4 ? (p->nchan + 3) / 4 * 4 : (p->nchan + 7) / 8 * 8;
     t.max_row = mfma_row_bytes(V.max_tiles);
     t.blocks = blocks;
+    if (V.id == kSmallDedispVariant) {
+        // estimated work-group time, from the tile-steps and flushed tiles of the records
+        const MfmaRec RL = mfma_rec(cps);
+        const int K = t.nchan_pad / cps;
+        for (const DmBlock& b : blocks) {
+            int64_t tile_steps = 0, flushed = 0;
+            for (int k = 0; k < K; ++k) {
+                int32_t tiles, left;
+                const uint8_t* rk = &rec[static_cast<size_t>(b.rec256) * 256 + static_cast<size_t>(k) * RL.size];
+                std::memcpy(&tiles, rk + RL.tiles, 4);
+                std::memcpy(&left, rk + RL.left, 4);
+                tile_steps += tiles;
+                if (left == 1) flushed += tiles;
+            }
+            add_estimate(t, blocks.size(), 3.11 + 0.357 * K + 0.0060 * tile_steps + 0.0305 * flushed + 0.135 * b.count);
+        }
+    }
     if (p->device >= 0) {
         std::vector<uint8_t> pad(t.max_row, 0x80);
         int rc = upload(&t.d_blocks, blocks);
@@ -809,6 +849,43 @@ int prepare_variant(aa_plan_s* p, int v) {
     }
     T = t;
     return AA_OK;
+}
+
+// A new plan's launches go to the strip kernel (variant 12) or to the step kernel (25), whichever
+// is estimated to end first: work-groups go round the CUs one at a time (either kernel's LDS fills
+// one), so that a launch takes the rounds of its work-groups, and its first round waits for cold
+// tables and rows besides. The strip kernel wins wherever there is much to do (3000 trials of
+// 4096 channels x 2^20 samples 106 against 230 ms). The step kernel wins where the work-group's
+// fixed part counts, which is smaller, and where its longer tiles (1024 against 864 samples)
+// need a round less. Measured, strip / step kernel in us at 2^18 samples: 4 channels, 100 trials 1
+// apart 658 / 463; 16 channels, 1 trial 19 / 9; 64 channels, 32 trials 1/16 apart 41 / 27 (two rounds
+// against one; 25 / 23 at 2^17 samples), 1 apart 107 / 146; 1024 channels, 1 trial 192 / 153; 128
+// channels, 100 trials 1 apart 305 / 447. The coefficients are fitted to 1970 launches of 1 to 1024
+// channels, 1 to 300 trials and 1000 to 2^20 samples in three bands: the kernel that they choose
+// takes 1.005 times the faster one's time in the geometric mean (3% of the launches over 1.06
+// times), the strip kernel 1.21 and the step kernel 1.08 times.
+int launch_variant(const aa_plan_s* p, int64_t n_out) {
+    const DedispTables& S = p->tables[kDefaultDedispVariant];
+    const DedispTables& T = p->tables[kSmallDedispVariant];
+    if (p->variant_chosen || p->variant != kDefaultDedispVariant || S.variant < 0 || T.variant < 0) return p->variant;
+    auto launch_us = [&](const DedispTables& t, int variant) {
+        const int64_t tile = kDedispVariants[variant].tile, cus = 256;
+        const int64_t groups = (n_out + t.span + tile - 1) / tile * static_cast<int64_t>(t.blocks.size());
+        return std::max(t.wg_max_us, static_cast<double>((groups + cus - 1) / cus) * t.wg_us);
+    };
+    const double strip = 5.76 + 1.09 * (S.nchan_pad / 16) + launch_us(S, kDefaultDedispVariant);
+    const double step = 2.43 + 0.043 * (S.nchan_pad / 16) + launch_us(T, kSmallDedispVariant);
+    return step < strip ? kSmallDedispVariant : kDefaultDedispVariant;
+}
+
+// With more than 64 channels and more than four blocks of trials the step kernel won one launch
+// of 98 (with up to four 15 of 182 by more than 10%): such plans, whose tables take time to make,
+// do without it.
+int prepare_default(aa_plan_s* p) {
+    int rc = prepare_variant(p, kDefaultDedispVariant);
+    if (rc == AA_OK && (p->nchan <= 64 || p->tables[kDefaultDedispVariant].blocks.size() <= 4))
+        rc = prepare_variant(p, kSmallDedispVariant);
+    return rc;
 }
 
 }  // namespace aa

@@ -85,6 +85,7 @@ extern "C" int aa_plan_set_variant(aa_plan_t p, int32_t v) {
     const int rc = prepare_variant(p, v);
     if (rc != AA_OK) return rc;
     p->variant = v;
+    p->variant_chosen = true;
     return AA_OK;
 }
 
@@ -179,6 +180,7 @@ extern "C" int aa_autotune(aa_plan_t p, const uint8_t* d_in, int64_t in_pitch, i
     if (rc != AA_OK) return rc;
     if (best < 0) return fail(AA_EINVAL, "aa_autotune: no variant could be prepared");
     p->variant = best;
+    p->variant_chosen = true;
     if (cache && *cache) {
         std::lock_guard<std::mutex> g(g_cache_mu);
         auto m = read_cache(cache);

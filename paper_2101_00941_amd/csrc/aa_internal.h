@@ -276,7 +276,9 @@ int build_quad_tables(const aa_plan_s* p, int tile, int chunks, std::vector<DmBl
 int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBlock>& blocks, std::vector<int32_t>& rs,
                        std::vector<uint32_t>& rec);
 void free_tables(DedispTables& t);
-// Launchers (dedisp.hip, sps.hip). Arguments are validated by the callers.
+// Launchers (dedisp.hip, sps.hip). Arguments are validated by the callers. Variant kPlanVariant:
+// the plan's, or what launch_variant gives the launch to.
+constexpr int kPlanVariant = -1;
 int launch_dedisperse(const aa_plan_s* p, int variant, const uint8_t* d_in, int64_t in_pitch, int64_t n_in,
                       int32_t* d_out, int64_t out_pitch, hipStream_t stream);
 DedispArgs dedisp_args(const aa_plan_s* p, int variant, const uint8_t* d_in, int64_t in_pitch, int64_t n_in,

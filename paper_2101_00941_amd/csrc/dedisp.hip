@@ -1051,6 +1051,7 @@ DedispArgs dedisp_args(const aa_plan_s* p, int variant, const uint8_t* d_in, int
 
 int launch_dedisperse(const aa_plan_s* p, int variant, const uint8_t* d_in, int64_t in_pitch, int64_t n_in,
                       int32_t* d_out, int64_t out_pitch, hipStream_t stream) {
+    if (variant == kPlanVariant) variant = launch_variant(p, n_in - p->maxshift);
     const DedispTables& T = p->tables[variant];
     if (T.variant != variant || !T.d_offs) return fail(AA_EINVAL, "aa_dedisperse: variant tables not prepared");
     const DedispVariant& V = kDedispVariants[variant];
@@ -1096,6 +1097,5 @@ extern "C" int aa_dedisperse(aa_plan_t p, const uint8_t* d_in, int64_t in_pitch,
         return fail(AA_EINVAL, "aa_dedisperse: d_in and in_pitch must be multiples of 16 bytes");
     if ((reinterpret_cast<uintptr_t>(d_out) & 15) || (out_pitch & 3) || out_pitch < n_in - p->maxshift)
         return fail(AA_EINVAL, "aa_dedisperse: d_out must be 16-byte aligned, out_pitch a multiple of 4 and >= n_out");
-    return launch_dedisperse(p, launch_variant(p, n_in - p->maxshift), d_in, in_pitch, n_in, d_out, out_pitch,
-                             static_cast<hipStream_t>(stream));
+    return launch_dedisperse(p, kPlanVariant, d_in, in_pitch, n_in, d_out, out_pitch, static_cast<hipStream_t>(stream));
 }

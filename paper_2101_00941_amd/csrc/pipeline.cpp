@@ -472,8 +472,7 @@ bool aa_pipeline_s::try_issue(Request* r, std::unique_lock<std::mutex>& lk) {
             }
         }
         if (launch) {
-            int rc = launch_dedisperse(p, launch_variant(p, n_in - p->maxshift), bm.buf[nb] + (w0 - h0n), bm.pitch, n_in,
-                                       dplane, opitch, s);
+            int rc = launch_dedisperse(p, kPlanVariant, bm.buf[nb] + (w0 - h0n), bm.pitch, n_in, dplane, opitch, s);
             if (rc == AA_OK)
                 rc = launch_single_pulse(p, dplane, opitch, w0, n_out, u.a, u.b, t_total, work_buf, dcand, cap, dcount,
                                          nullptr, 0, s);

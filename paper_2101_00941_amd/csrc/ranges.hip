@@ -323,7 +323,7 @@ extern "C" int aa_range_run(aa_range_plan_t rp, const uint8_t* d_in, int64_t in_
         const int64_t n = L.level_n[k];
         const int64_t n_out = n - p->maxshift, T = n_out - p->wmax + 1;
         const int64_t op = (n_out + 63) / 64 * 64;
-        rc = launch_dedisperse(p, launch_variant(p, n_out), x, xp, n, plane, op, stream);
+        rc = launch_dedisperse(p, kPlanVariant, x, xp, n, plane, op, stream);
         if (rc != AA_OK) return rc;
         rc = launch_single_pulse(p, plane, op, 0, n_out, 0, T, T, W + L.scratch, stage + static_cast<int64_t>(r) * stage_cap,
                                  stage_cap, counts + r, nullptr, 0, stream);

@@ -149,7 +149,8 @@ int aa_dedisperse(aa_plan_t plan, const uint8_t* d_in, int64_t in_pitch, int64_t
  *                                 estimate and keeps the fastest (ms_out holds that
  *                                 time). If AA_TUNE_CACHE names a file,
  *                                 the choice is read from and written to that JSON
- *                                 cache, keyed by device arch and plan shape.
+ *                                 cache, keyed by device arch, plan shape and set of
+ *                                 kernels (a choice made over other kernels is not used).
  * d_out receives the dedispersed plane of the last run.
  */
 typedef struct {

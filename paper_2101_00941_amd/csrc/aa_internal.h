@@ -263,6 +263,14 @@ int launch_variant(const aa_plan_s* p, int64_t n_out);
 // it on, the split taken from a cost estimate, or split_at when that is >= 0.
 int build_mfma_tables(const aa_plan_s* p, int tile, int depth, int max_tiles, int cps, std::vector<DmBlock>& blocks,
                       std::vector<int32_t>& rsv, std::vector<uint8_t>& rec, int split_at = -1, int* split_out = nullptr);
+// The autotuner's cache file: the choice for the plan's shape (variant -1: none; split of a
+// mixed-shape variant, else -1), as made over this build's set of kernels.
+struct TuneEntry {
+    int variant = -1, split = -1;
+};
+std::string tune_shape_key(const aa_plan_s* p, int64_t n_in);
+TuneEntry tune_cache_read(const char* path, const aa_plan_s* p, int64_t n_in);
+void tune_cache_write(const char* path, const aa_plan_s* p, int64_t n_in, const TuneEntry& e);
 // Rebuild the tables of a mixed-shape variant (layout 6) with its 4-channel blocks starting
 // at trial `split` (the autotuner's search around the host estimate).
 int prepare_mixed_split(aa_plan_s* p, int variant, int split);

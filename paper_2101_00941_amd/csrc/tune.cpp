@@ -2,7 +2,7 @@
 // shapes: waves per work-group x trials per wave, so trials per DM block, and the LDS
 // budget. The tuner times each variant with HIP events on the caller's stream and
 // keeps the fastest. A flat JSON cache, named by AA_TUNE_CACHE, remembers the
-// choice per (arch, plan shape).
+// choice per (arch, plan shape, set of kernels).
 #include <algorithm>
 #include <cstdio>
 #include <cstdlib>
@@ -18,17 +18,17 @@ namespace {
 
 std::mutex g_cache_mu;
 
-std::string cache_key(const aa_plan_s* p, int64_t n_in) {
-    hipDeviceProp_t prop;
-    std::string arch = "unknown";
-    if (hipGetDeviceProperties(&prop, p->device) == hipSuccess) arch = prop.gcnArchName;
-    const size_t colon = arch.find(':');
-    if (colon != std::string::npos) arch = arch.substr(0, colon);
+// The set of kernels that a choice was made over: a number for what the variants do, to be
+// raised when a variant's kernel is replaced or becomes faster or slower, and a hash of their
+// table (FNV-1a), which changes when variants are added or their shapes change.
+constexpr int kKernelRevision = 2;
+std::string kernel_set() {
+    uint64_t h = 14695981039346656037ull;
+    for (const DedispVariant& v : kDedispVariants)
+        for (int x : {v.id, v.waves, v.dpw, v.lds_bytes, v.layout, v.tile, v.depth, v.max_tiles})
+            h = (h ^ static_cast<uint32_t>(x)) * 1099511628211ull;
     std::ostringstream k;
-    // shape class: arch, channels, trials, maximum shift and the length in 2^k buckets
-    int lg = 0;
-    while ((int64_t{1} << (lg + 1)) <= n_in) ++lg;
-    k << arch << "|nchan=" << p->nchan << "|ndm=" << p->ndm << "|maxshift=" << p->maxshift << "|nin=2^" << lg;
+    k << "|kernels=" << kKernelRevision << "." << std::hex << h;
     return k.str();
 }
 
@@ -59,6 +59,43 @@ void write_cache(const char* path, const std::map<std::string, int>& m) {
 }
 
 }  // namespace
+
+std::string tune_shape_key(const aa_plan_s* p, int64_t n_in) {
+    hipDeviceProp_t prop;
+    std::string arch = "unknown";
+    if (p->device >= 0 && hipGetDeviceProperties(&prop, p->device) == hipSuccess) arch = prop.gcnArchName;
+    const size_t colon = arch.find(':');
+    if (colon != std::string::npos) arch = arch.substr(0, colon);
+    std::ostringstream k;
+    // shape class: arch, channels, trials, maximum shift and the length in 2^k buckets
+    int lg = 0;
+    while ((int64_t{1} << (lg + 1)) <= n_in) ++lg;
+    k << arch << "|nchan=" << p->nchan << "|ndm=" << p->ndm << "|maxshift=" << p->maxshift << "|nin=2^" << lg;
+    return k.str();
+}
+
+TuneEntry tune_cache_read(const char* path, const aa_plan_s* p, int64_t n_in) {
+    const std::string key = tune_shape_key(p, n_in) + kernel_set();
+    std::lock_guard<std::mutex> g(g_cache_mu);
+    const auto m = read_cache(path);
+    TuneEntry e;
+    const auto it = m.find(key);
+    if (it == m.end() || it->second < 0 || it->second >= kNumDedispVariants) return e;
+    e.variant = it->second;
+    const auto sp = m.find(key + "|split");
+    if (kDedispVariants[e.variant].layout == 6 && sp != m.end()) e.split = sp->second;
+    return e;
+}
+
+void tune_cache_write(const char* path, const aa_plan_s* p, int64_t n_in, const TuneEntry& e) {
+    const std::string key = tune_shape_key(p, n_in) + kernel_set();
+    std::lock_guard<std::mutex> g(g_cache_mu);
+    auto m = read_cache(path);
+    m[key] = e.variant;
+    if (kDedispVariants[e.variant].layout == 6) m[key + "|split"] = e.split;
+    write_cache(path, m);
+}
+
 }  // namespace aa
 
 using namespace aa;
@@ -101,17 +138,12 @@ extern "C" int aa_autotune(aa_plan_t p, const uint8_t* d_in, int64_t in_pitch, i
     if (p->device < 0) return fail(AA_EINVAL, "aa_autotune: plan was created host-only");
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     const char* cache = std::getenv("AA_TUNE_CACHE");
-    const std::string key = cache_key(p, n_in);
     if (cache && *cache) {
-        std::lock_guard<std::mutex> g(g_cache_mu);
-        const auto m = read_cache(cache);
-        const auto it = m.find(key);
-        if (it != m.end() && it->second >= 0 && it->second < kNumDedispVariants) {
-            int rc = aa_plan_set_variant(p, it->second);
-            const auto sp = m.find(key + "|split");
-            if (rc == AA_OK && sp != m.end() && kDedispVariants[it->second].layout == 6 &&
-                sp->second != p->tables[it->second].split)
-                rc = prepare_mixed_split(p, it->second, sp->second);
+        const TuneEntry e = tune_cache_read(cache, p, n_in);
+        if (e.variant >= 0) {
+            int rc = aa_plan_set_variant(p, e.variant);
+            if (rc == AA_OK && e.split >= 0 && e.split != p->tables[e.variant].split)
+                rc = prepare_mixed_split(p, e.variant, e.split);
             if (rc == AA_OK && ms_out)
                 for (int v = 0; v < kNumDedispVariants; ++v) ms_out[v] = -1.0f;
             if (rc == AA_OK) return aa_dedisperse(p, d_in, in_pitch, n_in, d_out, out_pitch, stream_);
@@ -181,12 +213,6 @@ extern "C" int aa_autotune(aa_plan_t p, const uint8_t* d_in, int64_t in_pitch, i
     if (best < 0) return fail(AA_EINVAL, "aa_autotune: no variant could be prepared");
     p->variant = best;
     p->variant_chosen = true;
-    if (cache && *cache) {
-        std::lock_guard<std::mutex> g(g_cache_mu);
-        auto m = read_cache(cache);
-        m[key] = best;
-        if (kDedispVariants[best].layout == 6) m[key + "|split"] = p->tables[best].split;
-        write_cache(cache, m);
-    }
+    if (cache && *cache) tune_cache_write(cache, p, n_in, TuneEntry{best, p->tables[best].split});
     return launch_dedisperse(p, best, d_in, in_pitch, n_in, d_out, out_pitch, stream);
 }

@@ -144,7 +144,8 @@ constexpr int quad_lds_bytes(int chunks) { return 2 * chunks * 1024; }
 //     R = 8: bits 3 i .. 3 i + 2 hold r of channel 4 (i / 2) + 2 h + i % 2 (substep i / 2);
 //            bits 12-21 and 22-31 hold e of the runs of substeps 0 and 1
 //   info: bit 0 / 1: substep 0 / 1 is its run's last (bit 1 copies bit 0 for R = 4);
-//     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e
+//     bits 2-5 / 6-9: strips - 1 of the run of substep 0 / 1; bits 10-19 / 20-29: its max e,
+//     which the strips follow from (for the host; the kernel reads the low ten bits)
 constexpr int kStripTile = 864;
 constexpr int kStripBias = 1024;         // bytes before the time tile that row starts stay within
 constexpr int kStripRows = 128;
@@ -172,7 +173,8 @@ inline bool variant_takes_pitch(int variant, int64_t in_pitch) {
 constexpr int kDefaultDedispVariant = 12;   // i8 matrix cores, strip kernel
 constexpr int kSmallDedispVariant = 25;     // the step kernel, for launches that launch_variant gives to it
 
-// Single-pulse-search tiling: a work-group covers kSpsRows DM rows and kSpsTile starts.
+// Single-pulse-search tiling: starts go in tiles of kSpsTile, of which the exact detection's
+// work-groups take kSpsRows DM rows each and the screened detection's waves runs of tiles.
 constexpr int kSpsTile = 256;
 constexpr int kSpsRows = 8;
 
@@ -279,7 +281,7 @@ int prepare_mixed_split(aa_plan_s* p, int variant, int split);
 int build_quad_tables(const aa_plan_s* p, int tile, int chunks, std::vector<DmBlock>& blocks,
                       std::vector<int32_t>& rec);
 // Host tables of the strip variant: DM blocks (cps 8 or 4: channels per matrix op; rec256 in
-// 256-byte units), row starts [nblk][nchan rounded up to 8] and the records. shape 0 takes
+// 256-byte units), row starts [nblk][nchan rounded up to 16] and the records. shape 0 takes
 // the cheaper shape per block by the cost estimate, 8 or 4 forces one.
 int build_strip_tables(const aa_plan_s* p, int tile, int shape, std::vector<DmBlock>& blocks, std::vector<int32_t>& rs,
                        std::vector<uint32_t>& rec);

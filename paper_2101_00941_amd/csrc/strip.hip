@@ -17,14 +17,16 @@
 //    addresses, phases or sign flips remain in the matrix loop.
 //  * A step is two groups of 8 channels and one barrier. The LDS ring holds two steps: in
 //    step k the contracting waves run the matrix ops of step k on operands already in
-//    registers and read those of step k + 1, while the staging waves store step k + 2. So no
-//    LDS latency is waited for within a step.
+//    registers and read those of step k + 1, while the staging waves store step k + 2. So a
+//    step's LDS reads are waited for once, with its barrier, and not between its matrix ops.
 // Measured against the 4 x 8 step kernel with 1024-sample tiles (variant 25): 4096 channels x
 // 2^20 samples, 3000 trials 106 ms (230 ms; 117 T byte-adds/s), 1500 trials of a 2^17-sample
 // chunk 5.8 ms (14.1 ms), 333 trials of 1001 channels x 77,777 samples 0.60 ms (0.96 ms). On the
-// chunk matrix cores are busy 31% of the SIMDs' cycles and other vector instructions 38%: about
-// ten go with a matrix operation, most of them window shifts; waits for the step barrier and
-// for operands make up the rest.
+// chunk matrix cores are busy 31% of the SIMDs' cycles, other vector instructions 38%, and 45% of
+// the waves' cycles are waits. About ten vector instructions go with a matrix operation: three
+// shift its window (tile 0 needs none), its share of the one-hot operand, which the four tiles
+// have in common, is 1.25 (8 channels x 4 residuals) or 3.5 to 4 (4 x 8), and the other half is
+// staging, flush and the loop. Launches with little to do are the step kernel's (launch_variant).
 #include "dedisp_device.h"
 
 namespace aa {

@@ -51,12 +51,11 @@ SAD_PEAK_TOPS = 4 * CU * LANES * CLOCK_GHZ / 1000.0
 I8_MFMA_PEAK_TOPS = 5000.0
 # HBM bytes per launch of the dedispersion kernel (FETCH_SIZE x 2.000 + WRITE_SIZE x
 # 1.000 per dispatch, scaled by a 1 GiB copy), from the counter runs summarised in
-# profiles/dedisp_*_survey_4096ch_1M.md. Keyed by (workload, variant), with the digest of
+# profiles/search_and_dedispersion.md. Keyed by (workload, variant), with the digest of
 # the kernel sources the counters were taken on: after any change to those sources the
 # entry no longer matches and the bench reports traffic as null.
 TRAFFIC_BYTES = {
-    ("survey_4096ch_1M", 20): (196.62e9 + 12.15e9, "2a64072bc06edccd"),
-    ("survey_4096ch_1M", 23): (466.86e9 + 12.15e9, "2a64072bc06edccd"),
+    ("survey_4096ch_1M", 12): (190.96e9 + 12.29e9, "b2d94c7b87992d55"),
 }
 KERNEL_SOURCES = ("dedisp.hip", "strip.hip", "dedisp_device.h", "tiling.cpp", "aa_internal.h", "xcd.h")
 # the part of aa_internal.h that the dedispersion kernels use: tiling constants, variant
@@ -642,13 +641,8 @@ def main():
     entry = TRAFFIC_BYTES.get((w["name"], plan.variant)) if not a.ndm else None
     traffic = entry[0] if entry and entry[1] == kernel_digest() else None
     if vinfo["layout"] in (4, 5, 6, 8):
-        # a contraction on the i8 matrix cores, priced against their dense peak; one op
-        # per useful byte add (the one-hot weights are not counted)
-        roofline = {"bound": "mfma", "dtype": "i8", "kernel": "dedisp_kernel (i8 matrix cores)",
-                    "achieved": achieved, "peak": I8_MFMA_PEAK_TOPS, "unit": "TOP/s",
-                    "frac": achieved / I8_MFMA_PEAK_TOPS, "traffic": traffic, "per_launch_ops": adds,
-                    "ms_per_launch": ms_dedisp, "alu_peak": ALU_PEAK_TOPS, "alu_frac": achieved / ALU_PEAK_TOPS,
-                    "hbm_frac": (ndm * n_dd * 4 + nchan * w["nsamp"]) / (ms_dedisp * 1e-3) / (HBM_PEAK_GBS * 1e9)}
+        roofline = mfma_roofline(vinfo["layout"], adds, ms_dedisp, ndm * n_dd * 4 + nchan * w["nsamp"])
+        roofline["traffic"] = traffic
     elif vinfo["layout"] == 7:
         roofline = quad_roofline(adds, ms_dedisp)
         roofline["traffic"] = traffic
@@ -709,6 +703,17 @@ def main():
 
 
 SURVEY_RANGES = ([0, 512, 1024, 1536, 2048, 2432], [1, 2, 4, 8, 16, 32])
+
+
+def mfma_roofline(layout, adds, ms, nbytes):
+    """Roofline of a contraction on the i8 matrix cores, priced against their dense peak; one op
+    per useful byte add (the one-hot weights are not counted). hbm_frac: the input read once
+    and the plane written once against the HBM peak."""
+    tops = adds / (ms * 1e-3) / 1e12
+    kernel = "dedisp_strip_kernel" if layout == 8 else "dedisp_kernel"
+    return {"bound": "mfma", "dtype": "i8", "kernel": f"{kernel} (i8 matrix cores)", "achieved": tops,
+            "peak": I8_MFMA_PEAK_TOPS, "unit": "TOP/s", "frac": tops / I8_MFMA_PEAK_TOPS, "traffic": None,
+            "per_launch_ops": adds, "ms_per_launch": ms, "hbm_frac": nbytes / (ms * 1e-3) / (HBM_PEAK_GBS * 1e9)}
 
 
 def quad_roofline(adds, ms):

@@ -201,6 +201,7 @@ struct DedispTables {
     int nchan_pad = 0;
     int32_t max_row = 0;
     std::vector<DmBlock> blocks;
+    void* d_mem = nullptr;           // the device tables' one allocation
     DmBlock* d_blocks = nullptr;
     int32_t* d_base = nullptr;
     int32_t* d_offs = nullptr;

@@ -3,6 +3,7 @@
 #include <algorithm>
 #include <climits>
 #include <cstring>
+#include <initializer_list>
 
 #include "aa_internal.h"
 
@@ -49,18 +50,41 @@ const DedispVariant kDedispVariants[kNumDedispVariants] = {
 };
 
 void free_tables(DedispTables& t) {
-    if (t.d_blocks) (void)hipFree(t.d_blocks);
-    if (t.d_base) (void)hipFree(t.d_base);
-    if (t.d_offs) (void)hipFree(t.d_offs);
-    if (t.d_pad) (void)hipFree(t.d_pad);
+    if (t.d_mem) (void)hipFree(t.d_mem);
     t = DedispTables();
 }
 
 namespace {
-template <class T>
-int upload(T** dst, const std::vector<T>& src) {
-    AA_HIP(hipMalloc(reinterpret_cast<void**>(dst), std::max<size_t>(src.size(), 1) * sizeof(T)));
-    AA_HIP(hipMemcpy(*dst, src.data(), src.size() * sizeof(T), hipMemcpyHostToDevice));
+// One table of a variant: where its device address goes, and its entries.
+struct TablePart {
+    void** dst;
+    const void* src;
+    size_t bytes;
+};
+template <class T, class U>
+TablePart part(T*& dst, const std::vector<U>& src) {
+    return TablePart{reinterpret_cast<void**>(&dst), src.data(), src.size() * sizeof(U)};
+}
+
+// A variant's tables in one allocation, each 256-byte aligned. Up to 1 MiB they are copied at
+// once: an allocation and a copy take about 15 us, which for a small plan is most of its making.
+int upload_tables(DedispTables& t, std::initializer_list<TablePart> parts) {
+    size_t total = 0;
+    for (const TablePart& p : parts) total += (p.bytes + 255) / 256 * 256;
+    AA_HIP(hipMalloc(&t.d_mem, std::max<size_t>(total, 256)));
+    uint8_t* const mem = static_cast<uint8_t*>(t.d_mem);
+    const bool at_once = total <= (size_t{1} << 20);
+    std::vector<uint8_t> all(at_once ? total : 0);
+    size_t off = 0;
+    for (const TablePart& p : parts) {
+        *p.dst = mem + off;
+        if (at_once && p.bytes)
+            std::memcpy(&all[off], p.src, p.bytes);
+        else if (p.bytes)
+            AA_HIP(hipMemcpy(mem + off, p.src, p.bytes, hipMemcpyHostToDevice));
+        off += (p.bytes + 255) / 256 * 256;
+    }
+    if (at_once && total) AA_HIP(hipMemcpy(mem, all.data(), total, hipMemcpyHostToDevice));
     return AA_OK;
 }
 }  // namespace
@@ -695,9 +719,7 @@ int prepare_strip(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     }
     t.blocks = blocks;
     if (p->device >= 0) {
-        int rc = upload(&t.d_blocks, blocks);
-        if (rc == AA_OK) rc = upload(&t.d_base, rs);
-        if (rc == AA_OK) rc = upload(reinterpret_cast<uint32_t**>(&t.d_offs), rec);
+        const int rc = upload_tables(t, {part(t.d_blocks, blocks), part(t.d_base, rs), part(t.d_offs, rec)});
         if (rc != AA_OK) return rc;
     }
     return AA_OK;
@@ -713,8 +735,7 @@ int prepare_quad(const aa_plan_s* p, const DedispVariant& V, DedispTables& t) {
     t.max_row = 0;
     t.blocks = blocks;
     if (p->device >= 0) {
-        int rc = upload(&t.d_blocks, blocks);
-        if (rc == AA_OK) rc = upload(&t.d_offs, rec);
+        const int rc = upload_tables(t, {part(t.d_blocks, blocks), part(t.d_offs, rec)});
         if (rc != AA_OK) return rc;
     }
     return AA_OK;
@@ -750,10 +771,8 @@ int prepare_mfma(const aa_plan_s* p, const DedispVariant& V, DedispTables& t, in
     }
     if (p->device >= 0) {
         std::vector<uint8_t> pad(t.max_row, 0x80);
-        int rc = upload(&t.d_blocks, blocks);
-        if (rc == AA_OK) rc = upload(&t.d_base, rsv);
-        if (rc == AA_OK) rc = upload(reinterpret_cast<uint8_t**>(&t.d_offs), rec);
-        if (rc == AA_OK) rc = upload(&t.d_pad, pad);
+        const int rc = upload_tables(t, {part(t.d_blocks, blocks), part(t.d_base, rsv), part(t.d_offs, rec),
+                                         part(t.d_pad, pad)});
         if (rc != AA_OK) return rc;
     }
     return AA_OK;
@@ -839,9 +858,7 @@ int prepare_variant(aa_plan_s* p, int v) {
     t.max_row = max_row;
     t.blocks = blocks;
     if (p->device >= 0) {
-        int rc = upload(&t.d_blocks, blocks);
-        if (rc == AA_OK) rc = upload(&t.d_base, base);
-        if (rc == AA_OK) rc = upload(&t.d_offs, offs);
+        const int rc = upload_tables(t, {part(t.d_blocks, blocks), part(t.d_base, base), part(t.d_offs, offs)});
         if (rc != AA_OK) {
             free_tables(t);
             return rc;
@@ -850,6 +867,23 @@ int prepare_variant(aa_plan_s* p, int v) {
     T = t;
     return AA_OK;
 }
+
+namespace {
+// Estimated time (us) of a launch over n_out samples: its work-groups' rounds of the CUs, and
+// what the first round takes besides.
+double launch_us(const aa_plan_s* p, int variant, int64_t n_out, size_t nblk, double wg_us, double wg_max_us) {
+    const int64_t tile = kDedispVariants[variant].tile, cus = 256;
+    const int32_t span = kDedispVariants[variant].layout == 8 ? p->tables[variant].span : 0;
+    const int64_t groups = (n_out + span + tile - 1) / tile * static_cast<int64_t>(nblk);
+    const int steps = (p->nchan + 15) / 16;
+    return std::max(wg_max_us, static_cast<double>((groups + cus - 1) / cus) * wg_us) +
+           (variant == kDefaultDedispVariant ? 5.76 + 1.09 * steps : 2.43 + 0.043 * steps);
+}
+double launch_us(const aa_plan_s* p, int variant, int64_t n_out) {
+    const DedispTables& t = p->tables[variant];
+    return launch_us(p, variant, n_out, t.blocks.size(), t.wg_us, t.wg_max_us);
+}
+}  // namespace
 
 // A new plan's launches go to the strip kernel (variant 12) or to the step kernel (25), whichever
 // is estimated to end first: work-groups go round the CUs one at a time (either kernel's LDS fills
@@ -865,27 +899,30 @@ int prepare_variant(aa_plan_s* p, int v) {
 // takes 1.005 times the faster one's time in the geometric mean (3% of the launches over 1.06
 // times), the strip kernel 1.21 and the step kernel 1.08 times.
 int launch_variant(const aa_plan_s* p, int64_t n_out) {
-    const DedispTables& S = p->tables[kDefaultDedispVariant];
-    const DedispTables& T = p->tables[kSmallDedispVariant];
-    if (p->variant_chosen || p->variant != kDefaultDedispVariant || S.variant < 0 || T.variant < 0) return p->variant;
-    auto launch_us = [&](const DedispTables& t, int variant) {
-        const int64_t tile = kDedispVariants[variant].tile, cus = 256;
-        const int64_t groups = (n_out + t.span + tile - 1) / tile * static_cast<int64_t>(t.blocks.size());
-        return std::max(t.wg_max_us, static_cast<double>((groups + cus - 1) / cus) * t.wg_us);
-    };
-    const double strip = 5.76 + 1.09 * (S.nchan_pad / 16) + launch_us(S, kDefaultDedispVariant);
-    const double step = 2.43 + 0.043 * (S.nchan_pad / 16) + launch_us(T, kSmallDedispVariant);
-    return step < strip ? kSmallDedispVariant : kDefaultDedispVariant;
+    if (p->variant_chosen || p->variant != kDefaultDedispVariant || p->tables[kDefaultDedispVariant].variant < 0 ||
+        p->tables[kSmallDedispVariant].variant < 0)
+        return p->variant;
+    return launch_us(p, kSmallDedispVariant, n_out) < launch_us(p, kDefaultDedispVariant, n_out) ? kSmallDedispVariant
+                                                                                               : kDefaultDedispVariant;
 }
 
-// With more than 64 channels and more than four blocks of trials the step kernel won one launch
-// of 98 (with up to four 15 of 182 by more than 10%): such plans, whose tables take time to make,
-// do without it.
+// The step kernel's tables are made for plans of up to 64 channels, whose launches it may win at
+// any length and whose tables are small, and for those of up to four blocks of trials where it may
+// win a launch over the plan's whole length: with the least that its work-groups can take, full
+// blocks of no drift. With more than 64 channels and more than four blocks it won one of the 98
+// launches that launch_variant was fitted to (with up to four 15 of 182 by more than 10%), and
+// 4096 channels' tables would double the time that a plan takes to make.
 int prepare_default(aa_plan_s* p) {
-    int rc = prepare_variant(p, kDefaultDedispVariant);
-    if (rc == AA_OK && (p->nchan <= 64 || p->tables[kDefaultDedispVariant].blocks.size() <= 4))
-        rc = prepare_variant(p, kSmallDedispVariant);
-    return rc;
+    const int rc = prepare_variant(p, kDefaultDedispVariant);
+    if (rc != AA_OK) return rc;
+    bool small = p->nchan <= 64;
+    if (!small && p->tables[kDefaultDedispVariant].blocks.size() <= 4) {
+        const int nblk = (p->ndm + 31) / 32, steps = (p->nchan + 3) / 4;
+        const double least = 3.11 + 0.357 * steps + 0.0060 * 32 * steps + 0.0305 * 32 + 0.135 * p->ndm / nblk;
+        small = launch_us(p, kSmallDedispVariant, p->n_dd, static_cast<size_t>(nblk), least, least) <
+                launch_us(p, kDefaultDedispVariant, p->n_dd);
+    }
+    return small ? prepare_variant(p, kSmallDedispVariant) : AA_OK;
 }
 
 }  // namespace aa

@@ -8,11 +8,11 @@ using namespace aa;
 
 static int bad = 0;
 
-static aa_plan_t make(int nchan, int ndm, double step, double band = 300.0) {
+static aa_plan_t make(int nchan, int ndm, double step, int64_t nsamp) {
     std::vector<double> dm;
     for (int i = 0; i < ndm; ++i) dm.push_back(step * i);
     aa_plan_desc_t d{};
-    d.nchan = nchan; d.nsamp = 1 << 24; d.f_top_mhz = 1450.0; d.foff_mhz = band / nchan; d.tsamp_s = 64e-6;
+    d.nchan = nchan; d.nsamp = nsamp; d.f_top_mhz = 1450.0; d.foff_mhz = 300.0 / nchan; d.tsamp_s = 64e-6;
     d.dm = dm.data(); d.ndm = ndm;
     int32_t widths[1] = {1};
     d.widths = widths; d.nwidths = 1; d.snr_threshold = 6.0f; d.flags = AA_PLAN_HOST_ONLY;
@@ -26,7 +26,10 @@ static void expect(const char* what, int got, int want) {
 }
 
 static void check(int nchan, int ndm, double step, int64_t n_out, int want) {
-    aa_plan_t p = make(nchan, ndm, step);
+    aa_plan_t probe = make(nchan, ndm, step, 1 << 24);
+    if (!probe) return;
+    aa_plan_t p = make(nchan, ndm, step, n_out + probe->maxshift);
+    aa_plan_destroy(probe);
     if (!p) return;
     char what[100];
     snprintf(what, sizeof(what), "%d channels, %d trials %g apart, %lld samples", nchan, ndm, step, static_cast<long long>(n_out));
@@ -63,6 +66,18 @@ int main() {
     check(1001, 333, 1.0, 77777, strip);
     check(4096, 100, 1.0 / 16, 1 << 17, strip);
     check(4096, 600, 1.0 / 16, 1 << 20, strip);
+    // few channels: also for launches shorter than the plan; many: no tables that are not used
+    aa_plan_t p = make(16, 1, 1.0, 1 << 24);
+    if (p) {
+        expect("a short launch of a long plan", launch_variant(p, 5000), step);
+        aa_plan_destroy(p);
+    }
+    p = make(4096, 100, 1.0 / 16, 1 << 20);
+    if (p) {
+        expect("tables of the step kernel", p->tables[step].variant, -1);
+        expect("a short launch without them", launch_variant(p, 5000), strip);
+        aa_plan_destroy(p);
+    }
     if (!bad) printf("ALL OK\n");
     return bad ? 1 : 0;
 }

@@ -896,7 +896,7 @@ double launch_us(const aa_plan_s* p, int variant, int64_t n_out) {
 // against one; 25 / 23 at 2^17 samples), 1 apart 107 / 146; 1024 channels, 1 trial 192 / 153; 128
 // channels, 100 trials 1 apart 305 / 447. The coefficients are fitted to 1970 launches of 1 to 1024
 // channels, 1 to 300 trials and 1000 to 2^20 samples in three bands: the kernel that they choose
-// takes 1.005 times the faster one's time in the geometric mean (3% of the launches over 1.06
+// takes 1.004 times the faster one's time in the geometric mean (1% of the launches over 1.06
 // times), the strip kernel 1.21 and the step kernel 1.08 times.
 int launch_variant(const aa_plan_s* p, int64_t n_out) {
     if (p->variant_chosen || p->variant != kDefaultDedispVariant || p->tables[kDefaultDedispVariant].variant < 0 ||
